@@ -2385,410 +2385,6 @@ __global__ __launch_bounds__(NTR) void k_bump_forces(T* const* __restrict__ fs, 
   }
 }
 
-// ---- nonlocal kernel regression (Eqs. 6.5-6.6) ---------------------------
-// The operator L_c[u](x) = sum over grid offsets 0 < |r| < delta of
-// K_c(|r|) (u(x + r) - u(x)), K_c = sum_m c_m B_m(|r| / delta) in the
-// Bernstein basis, and the features Phi_m[u] = sum_r B_m(|r| / delta)
-// (u(x + r) - u(x)) of its least-squares fit.  Offsets of equal |r|^2 form a
-// shell: Phi_m = sum_q W[m][q] (S_q - n_q u(x)) with S_q the sum of u over
-// shell q's offsets and n_q its size.
-//
-// A workgroup stages one tile of the periodic field and its halo of width R
-// (the largest offset component) in LDS, one displacement component at a
-// time; each thread owns two voxels of the tile (the second kNlTZ / 2 along z
-// in 3D, kNlTY2 / 2 along y in 2D).  Offsets arrive sorted by shell as LDS
-// index deltas, so the shell loop and the offset loop are uniform across the
-// workgroup.
-constexpr int kNlMaxDeg = 8;                                   // degree M
-constexpr int kNlMaxR = 6;                                     // horizon <= 7 voxels
-constexpr int kNlF = kNlMaxDeg + 1;
-constexpr int kNlTri = kNlF * (kNlF + 1) / 2;
-constexpr int kNlAcc = kNlTri + kNlF + 1;                      // G (upper), g, Gamma . Gamma
-constexpr int kNlTX = 8, kNlTY = 8, kNlTZ = 8;                 // 3D tile
-constexpr int kNlTX2 = 16, kNlTY2 = 32;                        // 2D tile
-constexpr int kNlGramBlocks = 2048;                            // fixed: the sum order never depends on the device
-
-struct NlGeom {
-  int nx, ny, nz, dim;
-  int tx, ty, tz;          // tile
-  int ntx, nty, ntz;       // tiles per axis
-  int R;                   // halo width
-  int lx, ly, lz;          // LDS box (tile + 2 R; lz = 1 in 2D)
-  int nshell;
-  int deg;
-  int vpt;                 // voxels per thread: 2, or 1 (tiles of half the voxels)
-};
-
-// Matrix form K1(|r|) I + K2(|r|) e e^T: 2 (M + 1) features per component,
-// one voxel per thread on tiles of 8 x 8 x 4 (3D) or 16 x 16 (2D), the
-// features of a tile in LDS rows of kNlFeatPitch doubles, and one Gram
-// entry per thread (the upper triangle row by row, then g, then
-// Gamma . Gamma).  The halo of its 3D normal equations is at most kNlMaxR1.
-constexpr int kNlF1 = 2 * kNlF;
-constexpr int kNlAcc1 = kNlF1 * (kNlF1 + 1) / 2 + kNlF1 + 1;
-constexpr int kNlMaxR1 = 4;
-constexpr int kNlTZ1 = 4, kNlTY21 = 16;
-constexpr int kNlFeatPitch = NTR + 1;
-static_assert(kNlAcc1 <= NTR, "one Gram entry per thread");
-
-template <typename T>
-__device__ __forceinline__ void nl_stage(const NlGeom& G, const T* __restrict__ ua, int x0, int y0, int z0, T* lds) {
-  const int nl = G.lx * G.ly * G.lz;
-  for (int i = threadIdx.x; i < nl; i += NTR) {
-    const int ix = i % G.lx, rest = i / G.lx;
-    const int iy = rest % G.ly, iz = rest / G.ly;
-    int gx = (x0 - G.R + ix) % G.nx;
-    int gy = (y0 - G.R + iy) % G.ny;
-    gx += gx < 0 ? G.nx : 0;
-    gy += gy < 0 ? G.ny : 0;
-    int gz = 0;
-    if (G.dim == 3) {
-      gz = (z0 - G.R + iz) % G.nz;
-      gz += gz < 0 ? G.nz : 0;
-    }
-    lds[i] = ua[((long long)gz * G.ny + gy) * G.nx + gx];
-  }
-}
-
-// tile `tile` of a field: origin and this thread's two voxels (local
-// coordinates, LDS index of each voxel's centre, validity)
-__device__ __forceinline__ void nl_tile(const NlGeom& G, int tile, int& x0, int& y0, int& z0, int (&vx)[2],
-                                        int (&vy)[2], int (&vz)[2], int (&base)[2], bool (&ok)[2]) {
-  const int tx = tile % G.ntx, rest = tile / G.ntx;
-  const int ty = rest % G.nty, tz = rest / G.nty;
-  x0 = tx * G.tx;
-  y0 = ty * G.ty;
-  z0 = tz * G.tz;
-  const int t = threadIdx.x;
-  const int lxv = t % G.tx, r2 = t / G.tx;
-#pragma unroll
-  for (int v = 0; v < 2; ++v) {
-    const int vv = (G.vpt == 2) ? v : 0;      // one voxel per thread: both slots name it
-    int ly, lz;
-    if (G.dim == 3) {
-      ly = r2 % G.ty;
-      lz = r2 / G.ty + vv * (G.tz / 2);
-    } else {
-      ly = r2 + vv * (G.ty / 2);
-      lz = 0;
-    }
-    vx[v] = x0 + lxv;
-    vy[v] = y0 + ly;
-    vz[v] = z0 + lz;
-    ok[v] = vx[v] < G.nx && vy[v] < G.ny && vz[v] < G.nz && (G.vpt == 2 || v == 0);
-    const int R = G.R, Rz = (G.dim == 3) ? G.R : 0;
-    base[v] = ((lz + Rz) * G.ly + (ly + R)) * G.lx + (lxv + R);
-  }
-}
-
-// shell sums minus n_q u(x) of both voxels, handed to fn(q, s0, s1)
-template <typename T, typename Fn>
-__device__ __forceinline__ void nl_shells(const NlGeom& G, const T* lds, const int (&base)[2],
-                                          const int* __restrict__ offs, const int* __restrict__ first, Fn&& fn) {
-  const double u0 = double(lds[base[0]]), u1 = double(lds[base[1]]);
-  for (int q = 0; q < G.nshell; ++q) {
-    const int o0 = first[q], o1 = first[q + 1];
-    double s0 = 0.0, s1 = 0.0;
-    for (int o = o0; o < o1; ++o) {
-      const int d = offs[o];
-      s0 += double(lds[base[0] + d]);
-      s1 += double(lds[base[1] + d]);
-    }
-    const double cnt = double(o1 - o0);
-    fn(q, s0 - cnt * u0, s1 - cnt * u1);
-  }
-}
-
-// Normal equations: each workgroup walks items (sample, tile) b, b + grid,
-// ... in order, accumulating per thread in FP64 the upper triangle of
-// Phi Phi^T, Phi . Gamma and Gamma . Gamma over its voxels and the
-// displacement components; the workgroup's sums go to its partial slot
-// (kNlAcc doubles, laid out for degree kNlMaxDeg).
-template <typename T>
-__global__ __launch_bounds__(NTR) void k_nl_gram(NlGeom G, const T* __restrict__ u, const T* __restrict__ gam,
-                                                 int nsample, const int* __restrict__ offs,
-                                                 const int* __restrict__ first, const double* __restrict__ W,
-                                                 double* __restrict__ partial) {
-  extern __shared__ __align__(16) unsigned char nl_smem[];
-  T* lds = reinterpret_cast<T*>(nl_smem);
-  const long long nvox = (long long)G.nx * G.ny * G.nz;
-  const int ntile = G.ntx * G.nty * G.ntz;
-  const int nf = G.deg + 1;
-  double acc[kNlAcc];
-#pragma unroll
-  for (int i = 0; i < kNlAcc; ++i) acc[i] = 0.0;
-  for (long long item = blockIdx.x; item < (long long)nsample * ntile; item += gridDim.x) {
-    const int k = int(item / ntile), tile = int(item % ntile);
-    int x0, y0, z0, vx[2], vy[2], vz[2], base[2];
-    bool ok[2];
-    nl_tile(G, tile, x0, y0, z0, vx, vy, vz, base, ok);
-    for (int a = 0; a < G.dim; ++a) {
-      const long long comp = ((long long)k * G.dim + a) * nvox;
-      __syncthreads();
-      nl_stage(G, u + comp, x0, y0, z0, lds);
-      __syncthreads();
-      double phi[2][kNlF];
-#pragma unroll
-      for (int v = 0; v < 2; ++v)
-#pragma unroll
-        for (int m = 0; m < kNlF; ++m) phi[v][m] = 0.0;
-      nl_shells(G, lds, base, offs, first, [&](int q, double s0, double s1) {
-#pragma unroll
-        for (int m = 0; m < kNlF; ++m) {
-          if (m < nf) {
-            const double w = W[m * G.nshell + q];
-            phi[0][m] += w * s0;
-            phi[1][m] += w * s1;
-          }
-        }
-      });
-#pragma unroll
-      for (int v = 0; v < 2; ++v) {
-        if (!ok[v]) continue;
-        const double gv = double(gam[comp + ((long long)vz[v] * G.ny + vy[v]) * G.nx + vx[v]]);
-        int i = 0;
-#pragma unroll
-        for (int m = 0; m < kNlF; ++m)
-#pragma unroll
-          for (int n2 = m; n2 < kNlF; ++n2, ++i) acc[i] += phi[v][m] * phi[v][n2];
-#pragma unroll
-        for (int m = 0; m < kNlF; ++m) acc[kNlTri + m] += phi[v][m] * gv;
-        acc[kNlTri + kNlF] += gv * gv;
-      }
-    }
-  }
-  // workgroup sum in a fixed order: waves by shuffles, then across waves
-  // (in the staging LDS, which holds at least kNlAcc NTR / 64 doubles)
-  double* red = reinterpret_cast<double*>(nl_smem);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kNlAcc; ++i) {
-    double v = acc[i];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) red[wave * kNlAcc + i] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < kNlAcc) {
-    double s = 0.0;
-    for (int w = 0; w < NTR / 64; ++w) s += red[w * kNlAcc + threadIdx.x];
-    partial[(long long)blockIdx.x * kNlAcc + threadIdx.x] = s;
-  }
-}
-
-// fixed-order sum of the partial slots (one workgroup): out[i] = sum over
-// slots of partial[slot stride + i], i < nacc
-__global__ __launch_bounds__(NTR) void k_nl_gram_sum(const double* __restrict__ partial, int nslot, int stride,
-                                                     int nacc, double* __restrict__ out) {
-  __shared__ double red[NTR / 64];
-  for (int i = 0; i < nacc; ++i) {
-    double a = 0.0;
-    for (int s = threadIdx.x; s < nslot; s += NTR) a += partial[(long long)s * stride + i];
-    const double sum = block_sum<NTR>(a, red);
-    if (threadIdx.x == 0) out[i] = sum;
-  }
-}
-
-// The fitted operator: out = sum_q kw[q] (S_q - n_q u(x)) per component,
-// kw[q] = K_c at shell q's radius; one workgroup per (sample, tile).
-template <typename T>
-__global__ __launch_bounds__(NTR) void k_nl_apply(NlGeom G, const T* __restrict__ u, int nsample,
-                                                  const int* __restrict__ offs, const int* __restrict__ first,
-                                                  const double* __restrict__ kw, T* __restrict__ out) {
-  extern __shared__ __align__(16) unsigned char nl_smem[];
-  T* lds = reinterpret_cast<T*>(nl_smem);
-  const long long nvox = (long long)G.nx * G.ny * G.nz;
-  const int ntile = G.ntx * G.nty * G.ntz;
-  const long long item = blockIdx.x;
-  if (item >= (long long)nsample * ntile) return;
-  const int k = int(item / ntile), tile = int(item % ntile);
-  int x0, y0, z0, vx[2], vy[2], vz[2], base[2];
-  bool ok[2];
-  nl_tile(G, tile, x0, y0, z0, vx, vy, vz, base, ok);
-  for (int a = 0; a < G.dim; ++a) {
-    const long long comp = ((long long)k * G.dim + a) * nvox;
-    __syncthreads();
-    nl_stage(G, u + comp, x0, y0, z0, lds);
-    __syncthreads();
-    double r0 = 0.0, r1 = 0.0;
-    nl_shells(G, lds, base, offs, first, [&](int q, double s0, double s1) {
-      const double w = kw[q];
-      r0 += w * s0;
-      r1 += w * s1;
-    });
-    if (ok[0]) out[comp + ((long long)vz[0] * G.ny + vy[0]) * G.nx + vx[0]] = T(r0);
-    if (ok[1]) out[comp + ((long long)vz[1] * G.ny + vy[1]) * G.nx + vx[1]] = T(r1);
-  }
-}
-
-// Normal equations of the matrix form.  Per staged input component b and
-// shell q: S = sum of (u_b(x + r) - u_b(x)) and T_a = sum of e_a e_b
-// (u_b(x + r) - u_b(x)), then Phi1[b][m] += W[m][q] S and Phi2[a][m] +=
-// W[m][q] T_a.  ee holds e_a e_b per offset as ee[(o 3 + b) 3 + a] (x
-// first, zero beyond the dimension).
-template <typename T>
-__global__ __launch_bounds__(NTR) void k_nl_gram1(NlGeom G, const T* __restrict__ u, const T* __restrict__ gam,
-                                                  int nsample, const int* __restrict__ offs,
-                                                  const int* __restrict__ first, const double* __restrict__ ee,
-                                                  const double* __restrict__ W, double* __restrict__ partial) {
-  extern __shared__ __align__(16) unsigned char nl_smem[];
-  double* feat = reinterpret_cast<double*>(nl_smem);          // [kNlF1][kNlFeatPitch]
-  double* gt = feat + kNlF1 * kNlFeatPitch;                    // [NTR]
-  T* lds = reinterpret_cast<T*>(gt + NTR);                     // staged box
-  const long long nvox = (long long)G.nx * G.ny * G.nz;
-  const int ntile = G.ntx * G.nty * G.ntz;
-  const int nf1 = G.deg + 1, nf = 2 * nf1;
-  const int ntri = nf * (nf + 1) / 2;
-  const int t = threadIdx.x;
-  // the Gram entry this thread owns
-  int kind = -1, ei = 0, ej = 0;
-  if (t < ntri) {
-    int i = 0, rem = t;
-    while (rem >= nf - i) {
-      rem -= nf - i;
-      ++i;
-    }
-    kind = 0;
-    ei = i;
-    ej = i + rem;
-  } else if (t < ntri + nf) {
-    kind = 1;
-    ei = t - ntri;
-  } else if (t == ntri + nf) {
-    kind = 2;
-  }
-  double acc = 0.0;
-  for (long long item = blockIdx.x; item < (long long)nsample * ntile; item += gridDim.x) {
-    const int k = int(item / ntile), tile = int(item % ntile);
-    int x0, y0, z0, vx[2], vy[2], vz[2], base[2];
-    bool ok[2];
-    nl_tile(G, tile, x0, y0, z0, vx, vy, vz, base, ok);
-    double p1[3][kNlF], p2[3][kNlF];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int m = 0; m < kNlF; ++m) {
-        p1[a][m] = 0.0;
-        p2[a][m] = 0.0;
-      }
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      if (b >= G.dim) break;
-      __syncthreads();
-      nl_stage(G, u + ((long long)k * G.dim + b) * nvox, x0, y0, z0, lds);
-      __syncthreads();
-      const double u0 = double(lds[base[0]]);
-      for (int q = 0; q < G.nshell; ++q) {
-        const int o0 = first[q], o1 = first[q + 1];
-        double S = 0.0, T0 = 0.0, T1 = 0.0, T2 = 0.0;
-        for (int o = o0; o < o1; ++o) {
-          const double dv = double(lds[base[0] + offs[o]]) - u0;
-          const double* e = ee + (o * 3 + b) * 3;
-          S += dv;
-          T0 += e[0] * dv;
-          T1 += e[1] * dv;
-          T2 += e[2] * dv;
-        }
-#pragma unroll
-        for (int m = 0; m < kNlF; ++m) {
-          if (m < nf1) {
-            const double w = W[m * G.nshell + q];
-            p1[b][m] += w * S;
-            p2[0][m] += w * T0;
-            p2[1][m] += w * T1;
-            p2[2][m] += w * T2;
-          }
-        }
-      }
-    }
-    // per output component: the tile's features into LDS, then every owner
-    // thread adds its entry's sum over the tile's voxels
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      if (a >= G.dim) break;
-      __syncthreads();
-#pragma unroll
-      for (int m = 0; m < kNlF; ++m) {
-        if (m < nf1) {
-          feat[m * kNlFeatPitch + t] = ok[0] ? p1[a][m] : 0.0;
-          feat[(nf1 + m) * kNlFeatPitch + t] = ok[0] ? p2[a][m] : 0.0;
-        }
-      }
-      gt[t] = ok[0] ? double(gam[((long long)k * G.dim + a) * nvox + ((long long)vz[0] * G.ny + vy[0]) * G.nx + vx[0]])
-                    : 0.0;
-      __syncthreads();
-      if (kind == 0) {
-        const double* fi = feat + ei * kNlFeatPitch;
-        const double* fj = feat + ej * kNlFeatPitch;
-        for (int v = 0; v < NTR; ++v) acc += fi[v] * fj[v];
-      } else if (kind == 1) {
-        const double* fi = feat + ei * kNlFeatPitch;
-        for (int v = 0; v < NTR; ++v) acc += fi[v] * gt[v];
-      } else if (kind == 2) {
-        for (int v = 0; v < NTR; ++v) acc += gt[v] * gt[v];
-      }
-    }
-  }
-  if (t < kNlAcc1) partial[(long long)blockIdx.x * kNlAcc1 + t] = (kind >= 0) ? acc : 0.0;
-}
-
-// The fitted matrix-form operator: out_a = sum over b and shells of
-// (K1_q delta_ab S_q + K2_q T_aq), kw1 / kw2 the two kernels at each
-// shell's radius; one workgroup per (sample, tile), two voxels per thread.
-template <typename T>
-__global__ __launch_bounds__(NTR) void k_nl_apply1(NlGeom G, const T* __restrict__ u, int nsample,
-                                                   const int* __restrict__ offs, const int* __restrict__ first,
-                                                   const double* __restrict__ ee, const double* __restrict__ kw1,
-                                                   const double* __restrict__ kw2, T* __restrict__ out) {
-  extern __shared__ __align__(16) unsigned char nl_smem[];
-  T* lds = reinterpret_cast<T*>(nl_smem);
-  const long long nvox = (long long)G.nx * G.ny * G.nz;
-  const int ntile = G.ntx * G.nty * G.ntz;
-  const long long item = blockIdx.x;
-  if (item >= (long long)nsample * ntile) return;
-  const int k = int(item / ntile), tile = int(item % ntile);
-  int x0, y0, z0, vx[2], vy[2], vz[2], base[2];
-  bool ok[2];
-  nl_tile(G, tile, x0, y0, z0, vx, vy, vz, base, ok);
-  double r[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-#pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    if (b >= G.dim) break;
-    __syncthreads();
-    nl_stage(G, u + ((long long)k * G.dim + b) * nvox, x0, y0, z0, lds);
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const double u0 = double(lds[base[v]]);
-      for (int q = 0; q < G.nshell; ++q) {
-        const int o0 = first[q], o1 = first[q + 1];
-        double S = 0.0, T0 = 0.0, T1 = 0.0, T2 = 0.0;
-        for (int o = o0; o < o1; ++o) {
-          const double dv = double(lds[base[v] + offs[o]]) - u0;
-          const double* e = ee + (o * 3 + b) * 3;
-          S += dv;
-          T0 += e[0] * dv;
-          T1 += e[1] * dv;
-          T2 += e[2] * dv;
-        }
-        const double w1 = kw1[q], w2 = kw2[q];
-        r[v][b] += w1 * S;
-        r[v][0] += w2 * T0;
-        r[v][1] += w2 * T1;
-        r[v][2] += w2 * T2;
-      }
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < 2; ++v) {
-    if (!ok[v]) continue;
-    const long long vox = ((long long)vz[v] * G.ny + vy[v]) * G.nx + vx[v];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-      if (a < G.dim) out[((long long)k * G.dim + a) * nvox + vox] = T(r[v][a]);
-  }
-}
-
 // ---- mixed-precision defect correction: FP64 state, FP32 inner solves ----
 // Wavevector of entry g of the packed half spectrum (xi_x = 0 on the kx = 0
 // column, which also carries the kx = H plane).
