@@ -93,7 +93,7 @@ struct lsfft_fno_s {
   float2* Hm[kMaxLayers] = {nullptr};
   float *p1 = nullptr, *z = nullptr, *y = nullptr, *dy = nullptr, *dz = nullptr, *sbuf = nullptr;
   float* dbuf[2] = {nullptr, nullptr};
-  float2 *t1 = nullptr, *t2 = nullptr, *ym = nullptr, *gm = nullptr, *tw = nullptr;
+  float2 *ym = nullptr, *gm = nullptr, *tw = nullptr;
   float* wpart = nullptr;
   int wblk = 0;
   double* lpart = nullptr;
@@ -193,12 +193,12 @@ hipError_t forward(lsfft_fno_s* f, int B, const float* x, float* y) {
   p.out = f->h[0];
   if ((e = launch_pointwise(p, f->stream)) != hipSuccess) return e;
   for (int l = 0; l < a.layers; ++l) {
-    if ((e = launch_dft_forward(n, M, BC, f->h[l], f->t1, f->t2, f->Hm[l], 1.0f, 1.0f, f->tw, f->stream)) != hipSuccess)
+    if ((e = launch_dft_forward(n, M, BC, f->h[l], f->Hm[l], 1.0f, 1.0f, f->tw, f->stream)) != hipSuccess)
       return e;
     if ((e = launch_modemix(0, f->Hm[l], f->rb[l], nullptr, reinterpret_cast<float*>(f->ym), f->L.nmodes, B,
                             f->stream)) != hipSuccess)
       return e;
-    if ((e = launch_dft_inverse(n, M, BC, f->ym, f->t2, f->t1, f->sbuf, inv_n3, 2.0f * inv_n3, f->tw, f->stream)) !=
+    if ((e = launch_dft_inverse(n, M, BC, f->ym, f->sbuf, inv_n3, 2.0f * inv_n3, f->tw, f->stream)) !=
         hipSuccess)
       return e;
     p = pw_args(f, f->L.hid[l], false, f->h[l], B);
@@ -242,7 +242,7 @@ hipError_t backward(lsfft_fno_s* f, int B, const float* x, const float* t) {
     const float* dpre = f->dbuf[cur];
     const Pw& hl = f->L.hid[l];
     if ((e = wgrad(f, hl, dpre, f->h[l], B)) != hipSuccess) return e;
-    if ((e = launch_dft_forward(n, M, BC, dpre, f->t1, f->t2, f->gm, inv_n3, 2.0f * inv_n3, f->tw, f->stream)) !=
+    if ((e = launch_dft_forward(n, M, BC, dpre, f->gm, inv_n3, 2.0f * inv_n3, f->tw, f->stream)) !=
         hipSuccess)
       return e;
     if ((e = launch_modemix(2, f->Hm[l], f->rb[l], f->gm, f->grads + f->L.r_off[l], f->L.nmodes, B, f->stream)) !=
@@ -251,7 +251,7 @@ hipError_t backward(lsfft_fno_s* f, int B, const float* x, const float* t) {
     if ((e = launch_modemix(1, f->gm, f->rb[l], nullptr, reinterpret_cast<float*>(f->ym), f->L.nmodes, B,
                             f->stream)) != hipSuccess)
       return e;
-    if ((e = launch_dft_inverse(n, M, BC, f->ym, f->t2, f->t1, f->sbuf, 1.0f, 1.0f, f->tw, f->stream)) != hipSuccess)
+    if ((e = launch_dft_inverse(n, M, BC, f->ym, f->sbuf, 1.0f, 1.0f, f->tw, f->stream)) != hipSuccess)
       return e;
     p = pw_args(f, hl, true, dpre, B);
     p.add = f->sbuf;
@@ -281,11 +281,11 @@ lsfft_status lsfft_fno_create(lsfft_fno_t* out, const lsfft_fno_arch* arch, int 
   f->a = *arch;
   f->max_batch = max_batch;
   f->stream = static_cast<hipStream_t>(hip_stream);
-  const int n = arch->n, M = arch->modes;
+  const int n = arch->n;
   f->V = (long long)n * n * n;
   f->L = make_layout(*arch);
   const size_t B = (size_t)max_batch, V = (size_t)f->V, C = kWidth, H = (size_t)arch->hidden;
-  const size_t nm = (size_t)f->L.nmodes;
+  const size_t nm = (size_t)f->L.nmodes, ns = (size_t)mode_slots(f->L.nmodes);
   bool ok = alloc(f, &f->params, f->L.nparam) && alloc(f, &f->grads, f->L.nparam) &&
             alloc(f, &f->mom, f->L.nparam) && alloc(f, &f->vel, f->L.nparam);
   auto pwb = [&](Pw& p) {
@@ -294,15 +294,14 @@ lsfft_status lsfft_fno_create(lsfft_fno_t* out, const lsfft_fno_arch* arch, int 
   ok = ok && pwb(f->L.lift) && pwb(f->L.proj1) && pwb(f->L.proj2);
   for (int l = 0; ok && l < arch->layers; ++l)
     ok = pwb(f->L.hid[l]) && alloc(f, &f->rb[l], nm * C * C * 2) && alloc(f, &f->pre[l], B * C * V) &&
-         alloc(f, &f->Hm[l], nm * B * C);
+         alloc(f, &f->Hm[l], ns * B * C);
   for (int l = 0; ok && l <= arch->layers; ++l) ok = alloc(f, &f->h[l], B * C * V);
   f->wblk = wgrad_blocks(max_batch, f->V);
   f->nchunk = 64;
   ok = ok && alloc(f, &f->p1, B * H * V) && alloc(f, &f->z, B * H * V) && alloc(f, &f->dz, B * H * V) &&
        alloc(f, &f->y, B * (size_t)arch->cout * V) && alloc(f, &f->dy, B * (size_t)arch->cout * V) &&
        alloc(f, &f->sbuf, B * C * V) && alloc(f, &f->dbuf[0], B * C * V) && alloc(f, &f->dbuf[1], B * C * V) &&
-       alloc(f, &f->t1, B * C * n * n * M) && alloc(f, &f->t2, B * C * n * 2 * M * M) &&
-       alloc(f, &f->ym, nm * B * C) && alloc(f, &f->gm, nm * B * C) && alloc(f, &f->tw, (size_t)n) &&
+       alloc(f, &f->ym, ns * B * C) && alloc(f, &f->gm, ns * B * C) && alloc(f, &f->tw, (size_t)n) &&
        alloc(f, &f->wpart, (size_t)f->wblk * (256 * 32 + 256)) &&
        alloc(f, &f->lpart, B * f->nchunk * 2 + B) && alloc(f, &f->loss_dev, 1);
   if (!ok) {
@@ -312,8 +311,8 @@ lsfft_status lsfft_fno_create(lsfft_fno_t* out, const lsfft_fno_arch* arch, int 
   }
   std::vector<float2> tw(n);
   for (int j = 0; j < n; ++j) {
-    const double ang = 2.0 * 3.14159265358979323846 * j / n;
-    tw[j] = make_float2((float)std::cos(ang), (float)std::sin(ang));
+    const double ang = 2.0 * 3.14159265358979323846 * j / n;   // exp(-i ang)
+    tw[j] = make_float2((float)std::cos(ang), -(float)std::sin(ang));
   }
   if (hipMemcpy(f->tw, tw.data(), sizeof(float2) * n, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemsetAsync(f->params, 0, sizeof(float) * f->L.nparam, f->stream) != hipSuccess ||

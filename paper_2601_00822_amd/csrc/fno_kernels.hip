@@ -10,6 +10,8 @@
 //       row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fft_core.hpp"
 #include "fno_launch.hpp"
 
@@ -17,6 +19,7 @@ namespace lsfft_fno {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NTB = 256;   // threads of the elementwise and transform kernels
 
@@ -308,486 +311,620 @@ hipError_t launch_wgrad(const WgArgs& a, float* gw, float* gb, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// per-mode complex products (one 64-thread block per mode)
+// per-mode complex products (one 256-thread block per eight modes)
 // ---------------------------------------------------------------------------
-// Operand tiles are staged in LDS as bf16 planes, A as [row][k] and B
-// transposed as [n][k], so every MFMA operand is one 16-byte LDS read.
+// The modes are kept as md[m / 8][bc][m % 8] (see the transforms below), so a
+// block reads and writes whole eight-mode groups as contiguous 16-byte runs,
+// and each of its four waves multiplies two modes.  Operands go through LDS as
+// bf16 planes, A as [row][k] and (mode 2) B transposed as [n][k], so every MFMA
+// operand is one 16-byte LDS read; the weights of modes 0 and 1 are read from
+// HBM straight into the operand registers.  Products leave through LDS in the
+// group layout.  HBM bounds it: at 6,912 modes and batch 32, 57 MB in, 28 MB of
+// weights, 57 MB out.
+constexpr int kMg = 8;                          // modes per group
+constexpr int kMixPitch = 32 + 8;               // bf16 plane row
+constexpr int kMixPlane = 32 * kMixPitch + 16;  // plane of one mode
+constexpr int kMixOut = kMg + 1;                // complex entries per bc of the staged products
+constexpr int kMixBytes0 = 1024 * kMixOut * 8;  // modes 0 and 1 (covers the two A planes)
+constexpr int kMixBytes2 = 4 * kMg * kMixPlane * 2;
+static_assert(2 * kMg * kMixPlane * 2 <= kMixBytes0, "operand planes under the staged products");
+
 template <int MODE>
-__global__ __launch_bounds__(64) void k_modemix(const float2* __restrict__ x, const __hip_bfloat16* __restrict__ rb,
-                                                const float2* __restrict__ g, float* __restrict__ out, int nmodes,
-                                                int B) {
-  __shared__ __attribute__((aligned(16))) __bf16 Ar[32][32 + 8], Ai[32][32 + 8], Br[32][32 + 8], Bi[32][32 + 8];
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(256) void k_modemix(const float2* __restrict__ x, const __hip_bfloat16* __restrict__ rb,
+                                                 const float2* __restrict__ g, float* __restrict__ out, int nmodes,
+                                                 int B) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __bf16* P = reinterpret_cast<__bf16*>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
-  const __bf16* r = reinterpret_cast<const __bf16*>(rb);
-  for (int m = blockIdx.x; m < nmodes; m += gridDim.x) {
-    const float2* xm = x + (size_t)m * B * 32;
-    const __bf16* rm = r + (size_t)m * 32 * 32 * 2;
-    if (MODE != 2) {
-      // B^T[n][k]: mode 0 -> R[k][n] (n = o, k = i); mode 1 -> conj R[n][k] (n = i, k = o)
-      for (int k = lane; k < 1024; k += 64) {
-        const int i = k >> 5, o = k & 31;
-        const __bf16 re = rm[2 * k], im = rm[2 * k + 1];
-        if (MODE == 0) { Br[o][i] = re; Bi[o][i] = im; }
-        else { Br[i][o] = re; Bi[i][o] = -im; }
-      }
-    }
-    f32x16 cr = {0}, ci = {0};
-    const int nbt = (B + 31) / 32;
-    for (int bt = 0; bt < nbt; ++bt) {
-      __syncthreads();
-      if (MODE != 2) {
-        // A[row = b][k]: mode 0 x[b][i], mode 1 g[b][o] (passed in x)
-        for (int k = lane; k < 1024; k += 64) {
-          const int rr = k >> 5, c = k & 31;
-          const int b = bt * 32 + rr;
-          const float2 v = (b < B) ? xm[(size_t)b * 32 + c] : make_float2(0.f, 0.f);
-          Ar[rr][c] = (__bf16)v.x;
-          Ai[rr][c] = (__bf16)v.y;
-        }
-      } else {
-        // A[row = i][k = b] = conj x[b][i]; B^T[n = o][k = b] = g[b][o]
-        const float2* gm = g + (size_t)m * B * 32;
-        for (int k = lane; k < 1024; k += 64) {
-          const int rr = k >> 5, c = k & 31;
-          const int b = bt * 32 + rr;
-          const float2 v = (b < B) ? xm[(size_t)b * 32 + c] : make_float2(0.f, 0.f);
-          const float2 w = (b < B) ? gm[(size_t)b * 32 + c] : make_float2(0.f, 0.f);
-          Ar[c][rr] = (__bf16)v.x;
-          Ai[c][rr] = (__bf16)(-v.y);
-          Br[c][rr] = (__bf16)w.x;
-          Bi[c][rr] = (__bf16)w.y;
-        }
-      }
-      __syncthreads();
+  const int grp = blockIdx.x;
+  const size_t BC = (size_t)B * 32;
+  const float4* x4 = reinterpret_cast<const float4*>(x + (size_t)grp * BC * kMg);
+  const float4* g4 = reinterpret_cast<const float4*>(g + (MODE == 2 ? (size_t)grp * BC * kMg : 0));
+  auto plane = [&](int which, int m) { return P + (which * kMg + m) * kMixPlane; };
+  const int nbt = (B + 31) / 32;
+
+  // weights of this wave's two modes as B operands:
+  // B^T[n][k]: mode 0 -> R[k][n] (n = o, k = i); mode 1 -> conj R[n][k] (n = i, k = o)
+  bf16x8 wr[MODE == 2 ? 1 : 2][2], wi[MODE == 2 ? 1 : 2][2];
+  if constexpr (MODE != 2) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int m = grp * kMg + wave * 2 + q;
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int k0 = s * 16 + half * 8;
-        const bf16x8 ar = *reinterpret_cast<const bf16x8*>(&Ar[col][k0]);
-        const bf16x8 ai = *reinterpret_cast<const bf16x8*>(&Ai[col][k0]);
-        const bf16x8 br = *reinterpret_cast<const bf16x8*>(&Br[col][k0]);
-        const bf16x8 bi = *reinterpret_cast<const bf16x8*>(&Bi[col][k0]);
-        cr = mfma(ar, br, cr);
-        cr = mfma(neg8(ai), bi, cr);
-        ci = mfma(ar, bi, ci);
-        ci = mfma(ai, br, ci);
+        unsigned w[8];
+        if (m < nmodes) {
+          const unsigned* rm = reinterpret_cast<const unsigned*>(rb) + (size_t)m * 1024;   // (re, im) pairs
+          if constexpr (MODE == 0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = rm[(k0 + j) * 32 + col];
+          } else {
+            const uint4 lo = reinterpret_cast<const uint4*>(rm + col * 32 + k0)[0];
+            const uint4 hi = reinterpret_cast<const uint4*>(rm + col * 32 + k0)[1];
+            w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
+            w[4] = hi.x; w[5] = hi.y; w[6] = hi.z; w[7] = hi.w;
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) w[j] = 0u;
+        }
+        union { unsigned short h[8]; bf16x8 v; } re, im;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          re.h[j] = (unsigned short)(w[j] & 0xffffu);
+          im.h[j] = (unsigned short)((w[j] >> 16) ^ (MODE == 1 ? 0x8000u : 0u));   // conj: sign flipped
+        }
+        wr[q][s] = re.v;
+        wi[q][s] = im.v;
       }
-      if (MODE != 2) {
-        float2* om = reinterpret_cast<float2*>(out) + (size_t)m * B * 32;
+    }
+  }
+
+  f32x16 cr[2], ci[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    cr[q] = f32x16{0};
+    ci[q] = f32x16{0};
+  }
+  for (int bt = 0; bt < nbt; ++bt) {
+    if (bt > 0) __syncthreads();
+    // 32 samples x 32 channels x 8 modes: thread t takes the mode pair t % 4
+    // of bc = t / 4, t / 4 + 64, ...
+    const int mp = tid & 3;
+#pragma unroll
+    for (int u0 = 0; u0 < 16; u0 += 4) {
+      float4 v[4], w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int bc = (tid >> 2) + 64 * (u0 + u);
+        const bool ok = bt * 32 + (bc >> 5) < B;
+        v[u] = w[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ok) {
+          v[u] = x4[((size_t)bt * 1024 + bc) * 4 + mp];
+          if constexpr (MODE == 2) w[u] = g4[((size_t)bt * 1024 + bc) * 4 + mp];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int bc = (tid >> 2) + 64 * (u0 + u);
+        const int rr = bc >> 5, c = bc & 31;
+        if constexpr (MODE != 2) {
+          // A[row = b][k]: mode 0 x[b][i], mode 1 g[b][o] (passed in x)
+          const int at = rr * kMixPitch + c;
+          plane(0, 2 * mp)[at] = (__bf16)v[u].x;
+          plane(1, 2 * mp)[at] = (__bf16)v[u].y;
+          plane(0, 2 * mp + 1)[at] = (__bf16)v[u].z;
+          plane(1, 2 * mp + 1)[at] = (__bf16)v[u].w;
+        } else {
+          // A[row = i][k = b] = conj x[b][i]; B^T[n = o][k = b] = g[b][o]
+          const int at = c * kMixPitch + rr;
+          plane(0, 2 * mp)[at] = (__bf16)v[u].x;
+          plane(1, 2 * mp)[at] = (__bf16)(-v[u].y);
+          plane(0, 2 * mp + 1)[at] = (__bf16)v[u].z;
+          plane(1, 2 * mp + 1)[at] = (__bf16)(-v[u].w);
+          plane(2, 2 * mp)[at] = (__bf16)w[u].x;
+          plane(3, 2 * mp)[at] = (__bf16)w[u].y;
+          plane(2, 2 * mp + 1)[at] = (__bf16)w[u].z;
+          plane(3, 2 * mp + 1)[at] = (__bf16)w[u].w;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int m = wave * 2 + q;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int at = col * kMixPitch + s * 16 + half * 8;
+        const bf16x8 ar = *reinterpret_cast<const bf16x8*>(plane(0, m) + at);
+        const bf16x8 ai = *reinterpret_cast<const bf16x8*>(plane(1, m) + at);
+        bf16x8 br, bi;
+        if constexpr (MODE == 2) {
+          br = *reinterpret_cast<const bf16x8*>(plane(2, m) + at);
+          bi = *reinterpret_cast<const bf16x8*>(plane(3, m) + at);
+        } else {
+          br = wr[q][s];
+          bi = wi[q][s];
+        }
+        cr[q] = mfma(ar, br, cr[q]);
+        cr[q] = mfma(neg8(ai), bi, cr[q]);
+        ci[q] = mfma(ar, bi, ci[q]);
+        ci[q] = mfma(ai, br, ci[q]);
+      }
+    }
+    if constexpr (MODE != 2) {
+      __syncthreads();   // the planes have been read: the products replace them
+      float2* so = reinterpret_cast<float2*>(smem);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int rr = 8 * (e / 4) + 4 * half + (e % 4);
-          const int b = bt * 32 + rr;
-          if (b < B) om[(size_t)b * 32 + col] = make_float2(cr[e], ci[e]);
+          so[(rr * 32 + col) * kMixOut + wave * 2 + q] = make_float2(cr[q][e], ci[q][e]);
         }
-        cr = f32x16{0};
-        ci = f32x16{0};
+        cr[q] = f32x16{0};
+        ci[q] = f32x16{0};
+      }
+      __syncthreads();
+      float4* o4 = reinterpret_cast<float4*>(reinterpret_cast<float2*>(out) + (size_t)grp * BC * kMg);
+#pragma unroll 4
+      for (int u = 0; u < 16; ++u) {
+        const int bc = (tid >> 2) + 64 * u;
+        if (bt * 32 + (bc >> 5) >= B) continue;
+        const float2 p = so[bc * kMixOut + 2 * mp], r = so[bc * kMixOut + 2 * mp + 1];
+        o4[((size_t)bt * 1024 + bc) * 4 + mp] = make_float4(p.x, p.y, r.x, r.y);
       }
     }
-    if (MODE == 2) {
+  }
+  if constexpr (MODE == 2) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int m = grp * kMg + wave * 2 + q;
+      if (m >= nmodes) continue;
       float2* om = reinterpret_cast<float2*>(out) + (size_t)m * 32 * 32;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int i = 8 * (e / 4) + 4 * half + (e % 4);
-        om[i * 32 + col] = make_float2(cr[e], ci[e]);
+        om[i * 32 + col] = make_float2(cr[q][e], ci[q][e]);
       }
     }
-    __syncthreads();
   }
+}
+
+template <typename K>
+static hipError_t allow_lds(K kernel, size_t bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
 }
 
 hipError_t launch_modemix(int mode, const float2* x, const __hip_bfloat16* r, const float2* g, float* out,
                           int nmodes, int B, hipStream_t s) {
-  const dim3 grid((unsigned)(nmodes < 65536 ? nmodes : 65536));
-  if (mode == 0) hipLaunchKernelGGL(k_modemix<0>, grid, 64, 0, s, x, r, g, out, nmodes, B);
-  else if (mode == 1) hipLaunchKernelGGL(k_modemix<1>, grid, 64, 0, s, x, r, g, out, nmodes, B);
-  else if (mode == 2) hipLaunchKernelGGL(k_modemix<2>, grid, 64, 0, s, x, r, g, out, nmodes, B);
-  else return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((nmodes + kMg - 1) / kMg));
+  hipError_t e;
+  if (mode == 0) {
+    if ((e = allow_lds(k_modemix<0>, kMixBytes0)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_modemix<0>, grid, 256, kMixBytes0, s, x, r, g, out, nmodes, B);
+  } else if (mode == 1) {
+    if ((e = allow_lds(k_modemix<1>, kMixBytes0)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_modemix<1>, grid, 256, kMixBytes0, s, x, r, g, out, nmodes, B);
+  } else if (mode == 2) {
+    if ((e = allow_lds(k_modemix<2>, kMixBytes2)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_modemix<2>, grid, 256, kMixBytes2, s, x, r, g, out, nmodes, B);
+  } else {
+    return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// truncated transforms: length-N FFTs along one axis at a time, fp32
+// truncated transforms: one cube of one (sample, channel) per workgroup
 // ---------------------------------------------------------------------------
-// Every kernel transforms a tile of MP pencils with the solver's Stockham
-// tile transform (fft_core.hpp): full pencils are loaded (the truncated
-// inputs of an inverse as zeros), transformed in registers and LDS, and only
-// the kept outputs are stored.  Layouts (BC = batch x channels, P = 2M M):
-//   h   [BC][z][y][x]           real
-//   t1  [BC][z][y][kx]          kx < M
-//   t2  [BC][z][iy][kx]         iy < 2M (signed ky)
-//   md  [iz P + iy M + kx][BC]  the kept modes, mode-major
-// Kept array index of the signed wavenumber slot s in [0, 2M): s for s < M,
-// n - 2M + s for the negative ones; the slot of FFT index k is k for k < M,
-// k - n + 2M for k >= n - M, none otherwise.
-template <int N> __device__ __forceinline__ int kidx(int s, int M) { return s < M ? s : N - 2 * M + s; }
-template <int N> __device__ __forceinline__ int kslot(int k, int M) {
+// All three axes of a cube in one launch, the truncated spectrum between the
+// axes in LDS: a thread holds one pencil of N points in registers and runs the
+// whole length-N Stockham transform there (the radices and operations of the
+// solver's plans), so LDS only carries the kept entries from one axis to the
+// next, in place.  One launch per axis through HBM moved 541 MB per batch of
+// 32 at N = 32, M = 12 (45 + 31 + 38 us forward, 32 + 32 + 55 us inverse)
+// where 191 MB are needed; a cube takes one launch of 62 us forward and 56
+// inverse.  Registers allow two waves per SIMD, and the three phases' transforms
+// (VALU) and their LDS exchange, one after the other, bound it.
+//
+// LDS entry (z, y or iy, kx) of the cube sits at z PP + y MP + kx: MP odd, so
+// the lanes of the x phase (one row each) fall on different banks, and PP = M
+// modulo 16, so that consecutive pencils of the y phase are consecutive across
+// planes too.
+//
+//   h, out  [BC][z][y][x]                 real
+//   md      [m / 8][BC][m % 8]            the kept modes m = iz P + iy M + kx,
+//                                         P = 2 M^2, iy and iz in [0, 2M)
+// Kept array index of FFT index k: k for k < M, k - n + 2M for k >= n - M.
+template <int N> __device__ __forceinline__ constexpr int kslot(int k, int M) {
   return k < M ? k : (k >= N - M ? k - N + 2 * M : -1);
 }
+template <int N> constexpr int cube_threads() { return N * N < 512 ? N * N : 512; }
 
-// twiddles exp(-2 pi i k / N) split into LDS as the tile transform reads
-// them, from the (cos, sin) table of the surrogate
-template <int N>
-__device__ __forceinline__ void load_tw_split(float* twr, float* twi, const float2* twg) {
-  for (int k = threadIdx.x; k < N; k += NTB) {
-    const float2 w = twg[k];
-    twr[k] = w.x;
-    twi[k] = -w.y;
-  }
+// a product rounded by itself, whatever is added to it next
+__device__ __forceinline__ float scaled(float x, float c) {
+#pragma clang fp contract(off)
+  return x * c;
 }
 
-// x axis: MX rows of N reals per tile, index-fastest butterflies (each
-// row's points come from consecutive lanes)
-template <int N> struct XT {
-  static constexpr int MP = 2048 / N;
-  static constexpr int SM = N + 1;
-  template <int DIR> using F = lsfft::TileFft<float, N, DIR, false, MP, SM, 1, 1, true, NTB>;
-};
-// y and z axes: 64 pencils per tile, pencil-fastest butterflies
-constexpr int kPen = 64;
-template <int N> struct ST {
-  static constexpr int SN = kPen + 1;
-  template <int DIR> using F = lsfft::TileFft<float, N, DIR, false, kPen, 1, SN, 1, false, NTB>;
+// The twiddles exp(-2 pi i k / N) that the second pass uses, in scalar
+// registers for the whole kernel: left to the compiler they are vector loads
+// inside every transform, whose waits also wait for the next cube's rows.
+template <int N> struct RegTw {
+  static constexpr int CNT = lsfft::Plan<N>::np == 1 ? 1 : (lsfft::Plan<N>::r1 - 1) * (N / lsfft::Plan<N>::r1 - 1) + 1;
+  float r[CNT], i[CNT];
+  __device__ __forceinline__ void load(const float2* __restrict__ tw) {
+#pragma unroll
+    for (int k = 0; k < CNT; ++k) {
+      const float2 w = tw[k];
+      r[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(w.x)));
+      i[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(w.y)));
+    }
+  }
 };
 
-// x forward: rows of reals -> kx < M
-template <int N>
-__global__ __launch_bounds__(NTB) void k_dft_x_fwd(const float* __restrict__ h, float2* __restrict__ t1, long long rows,
-                                                   int M, const float2* __restrict__ twg) {
-  using F = typename XT<N>::template F<-1>;
-  constexpr int MP = XT<N>::MP;
-  __shared__ float re[MP * XT<N>::SM], im[MP * XT<N>::SM], twr[N], twi[N];
-  load_tw_split<N>(twr, twi, twg);
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const long long row0 = (long long)blockIdx.x * MP;
-  float in_r[F::B0][F::R0], in_i[F::B0][F::R0];
+template <int N, int DIR> struct RegFft {
+  using P = lsfft::Plan<N>;
+  static_assert(P::np <= 2, "two-pass plans");
+  // positions 0..N-1 in and out
+  __device__ static __forceinline__ void run(float (&vr)[N], float (&vi)[N], const RegTw<N>& tw) {
+    constexpr int R0 = P::r0, R1 = P::r1;
+    if constexpr (P::np == 1) {
+      lsfft::bfly<float, R0, DIR>(vr, vi);
+    } else {
+      float tr[N], ti[N];
 #pragma unroll
-  for (int q = 0; q < F::B0; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::R0>(b, m, j);
-    const bool ok = (F::TOT0 % NTB == 0 || b < F::TOT0) && row0 + m < rows;
+      for (int j = 0; j < N / R0; ++j) {
+        float ar[R0], ai[R0];
 #pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      in_r[q][r] = ok ? h[(row0 + m) * N + j + r * (N / F::R0)] : 0.0f;
-      in_i[q][r] = 0.0f;
-    }
-  }
-  float o_r[F::BL][F::RL], o_i[F::BL][F::RL];
-  F::run(in_r, in_i, o_r, o_i, re, im, twr, twi, tid);
+        for (int r = 0; r < R0; ++r) {
+          ar[r] = vr[j + r * (N / R0)];
+          ai[r] = vi[j + r * (N / R0)];
+        }
+        lsfft::bfly<float, R0, DIR>(ar, ai);
 #pragma unroll
-  for (int q = 0; q < F::BL; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::RL>(b, m, j);
-    if ((F::TOTL % NTB == 0 || b < F::TOTL) && row0 + m < rows) {
+        for (int r = 0; r < R0; ++r) {
+          tr[j * R0 + r] = ar[r];
+          ti[j * R0 + r] = ai[r];
+        }
+      }
 #pragma unroll
-      for (int r = 0; r < F::RL; ++r) {
-        const int k = j + r * (N / F::RL);
-        if (k < M) t1[(row0 + m) * M + k] = make_float2(o_r[q][r], o_i[q][r]);
+      for (int j = 0; j < N / R1; ++j) {
+        float ar[R1], ai[R1];
+#pragma unroll
+        for (int r = 0; r < R1; ++r) {
+          ar[r] = tr[j + r * (N / R1)];
+          ai[r] = ti[j + r * (N / R1)];
+        }
+#pragma unroll
+        for (int r = 1; r < R1; ++r) {
+          const float br = tw.r[r * j], bi = (DIR < 0) ? tw.i[r * j] : -tw.i[r * j];
+          // (rounded as the tile transforms round it, so the bits do not depend on
+          // what the compiler contracts here)
+          const float t = __builtin_fmaf(ar[r], br, -scaled(ai[r], bi));
+          ai[r] = __builtin_fmaf(ai[r], br, scaled(ar[r], bi));
+          ar[r] = t;
+        }
+        lsfft::bfly<float, R1, DIR>(ar, ai);
+#pragma unroll
+        for (int r = 0; r < R1; ++r) {
+          vr[j + r * (N / R1)] = ar[r];
+          vi[j + r * (N / R1)] = ai[r];
+        }
       }
     }
   }
+};
+
+struct CubeArgs {
+  int M, BC;
+  int MP, PP;      // LDS pitches of a row and of a plane (complex entries)
+  float s0, s1;    // scale of kx = 0 and of kx > 0
+  const float2* tw;
+};
+__device__ __forceinline__ size_t md_at(int m, int bc, int BC) {
+  return ((size_t)(m >> 3) * BC + bc) * kMg + (m & 7);
+}
+// Blocks of one XCD take consecutive cubes: their 64-byte runs of a mode group
+// then meet in that XCD's L2.
+__device__ __forceinline__ int cube_slot(int b, int G) {
+  const int q = G / 8, r = G % 8, x = b % 8;
+  return x * q + (x < r ? x : r) + b / 8;
 }
 
-// x inverse: out[row][x] = sum_kx c(kx) Re(t1[row][kx] e^{+i kx x}),
-// c(0) = c0, c(kx > 0) = c1
+// A wave's 64 rows between HBM and one row per lane, through a wave-private
+// stretch of LDS (its own rows of the cube: no barrier), 16 entries at a time at
+// a pitch of 20 words.  HBM sees 64-byte runs of four lanes; a row per lane
+// straight from HBM touches 64 lines per access and keeps 64 KB of them open,
+// twice the L1 (the inverse took 72 us per batch of 32 at N = 32 that way).
+constexpr int kRowPitch = 20, kRowStage = 64 * kRowPitch * 4;   // words, bytes per wave
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 template <int N>
-__global__ __launch_bounds__(NTB) void k_dft_x_inv(const float2* __restrict__ t1, float* __restrict__ out, long long rows,
-                                                   int M, float c0, float c1, const float2* __restrict__ twg) {
-  using F = typename XT<N>::template F<+1>;
-  constexpr int MP = XT<N>::MP;
-  __shared__ float re[MP * XT<N>::SM], im[MP * XT<N>::SM], twr[N], twi[N];
-  load_tw_split<N>(twr, twi, twg);
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const long long row0 = (long long)blockIdx.x * MP;
-  float in_r[F::B0][F::R0], in_i[F::B0][F::R0];
+__device__ __forceinline__ void rows_fetch(const float* __restrict__ src, f32x4 (&v)[N / 4], int lane) {
+  // piece i of 16 entries: rows (i % 4) * 16 + lane / 4, entries 16 (i / 4) + 4 (lane % 4)
 #pragma unroll
-  for (int q = 0; q < F::B0; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::R0>(b, m, j);
-    const bool ok = (F::TOT0 % NTB == 0 || b < F::TOT0) && row0 + m < rows;
+  for (int i = 0; i < N / 4; ++i)
+    v[i] = *reinterpret_cast<const f32x4*>(src + ((i & 3) * 16 + (lane >> 2)) * N + (i >> 2) * 16 + 4 * (lane & 3));
+}
+template <int N>
+__device__ __forceinline__ void rows_spread(const f32x4 (&v)[N / 4], float (&row)[N], float* st, int lane) {
 #pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      const int k = j + r * (N / F::R0);
-      float2 v = make_float2(0.0f, 0.0f);
-      if (ok && k < M) {
-        v = t1[(row0 + m) * M + k];
-        const float c = (k == 0) ? c0 : c1;
-        v.x *= c;
-        v.y *= c;
+  for (int hh = 0; hh < N / 16; ++hh) {
+    wave_order();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4*>(st + (i * 16 + (lane >> 2)) * kRowPitch + 4 * (lane & 3)) = v[hh * 4 + i];
+    wave_order();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(st + lane * kRowPitch + 4 * k);
+      row[hh * 16 + 4 * k] = x.x;
+      row[hh * 16 + 4 * k + 1] = x.y;
+      row[hh * 16 + 4 * k + 2] = x.z;
+      row[hh * 16 + 4 * k + 3] = x.w;
+    }
+  }
+  wave_order();
+}
+template <int N>
+__device__ __forceinline__ void rows_store(float* __restrict__ dst, const float (&row)[N], float* st, int lane) {
+#pragma unroll
+  for (int hh = 0; hh < N / 16; ++hh) {
+    wave_order();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      *reinterpret_cast<float4*>(st + lane * kRowPitch + 4 * k) =
+          make_float4(row[hh * 16 + 4 * k], row[hh * 16 + 4 * k + 1], row[hh * 16 + 4 * k + 2], row[hh * 16 + 4 * k + 3]);
+    wave_order();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<float4*>(dst + (i * 16 + (lane >> 2)) * N + hh * 16 + 4 * (lane & 3)) =
+          *reinterpret_cast<const float4*>(st + (i * 16 + (lane >> 2)) * kRowPitch + 4 * (lane & 3));
+  }
+  wave_order();
+}
+
+// h -> kept modes.  The next cube's rows are in flight during the y and z
+// phases.
+template <int N>
+__global__ __launch_bounds__(cube_threads<N>()) void k_cube_fwd(const float* __restrict__ h, float2* __restrict__ md,
+                                                                CubeArgs a) {
+  constexpr int NT = cube_threads<N>(), RPT = N * N / NT;
+  static_assert(RPT <= 2, "two rows per thread");
+  extern __shared__ __align__(16) unsigned char smem[];
+  float2* L = reinterpret_cast<float2*>(smem);
+  RegTw<N> tw;
+  tw.load(a.tw);
+  const int M = a.M, P = 2 * M * M;
+  constexpr bool STG = N >= 16;                       // 8-point rows go straight
+  auto load = [&](int bc, int q, int wave, int lane, f32x4 (&v)[N / 4]) {
+    const float* src = h + ((size_t)bc * N * N + wave * 64 + q * NT) * N;
+    if constexpr (STG) {
+      rows_fetch<N>(src, v, lane);
+    } else {
+#pragma unroll
+      for (int k = 0; k < N / 4; ++k) v[k] = reinterpret_cast<const f32x4*>(src + lane * N)[k];
+    }
+  };
+  int bc = cube_slot(blockIdx.x, gridDim.x);
+  f32x4 in[RPT][N / 4];
+  if (bc < a.BC) {
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) load(bc, q, threadIdx.x >> 6, threadIdx.x & 63, in[q]);
+  }
+  for (; bc < a.BC; bc += gridDim.x) {
+    // opaque: what follows from the thread's number is formed in every cube, not
+    // kept in registers (and spilled) across all of them
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+      float vr[N], vi[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) vi[k] = 0.0f;
+      const int r0 = wave * 64 + q * NT;              // this wave's first row
+      if constexpr (STG) {
+        rows_spread<N>(in[q], vr, reinterpret_cast<float*>(L + (r0 / N) * a.PP), lane);
+      } else {
+#pragma unroll
+        for (int k = 0; k < N / 4; ++k) {
+          vr[4 * k] = in[q][k].x;
+          vr[4 * k + 1] = in[q][k].y;
+          vr[4 * k + 2] = in[q][k].z;
+          vr[4 * k + 3] = in[q][k].w;
+        }
       }
-      in_r[q][r] = v.x;
-      in_i[q][r] = v.y;
+      RegFft<N, -1>::run(vr, vi, tw);
+      // the upper half is formed too, as everywhere else: left out, its
+      // partners' products have one use and are contracted into other roundings
+#pragma unroll
+      for (int k = N / 2; k < N; ++k) asm volatile("" ::"v"(vr[k]), "v"(vi[k]));
+      const int r = tid + q * NT;
+      float2* dst = L + (r / N) * a.PP + (r % N) * a.MP;
+#pragma unroll
+      for (int k = 0; k < N / 2; ++k)
+        if (k < M) dst[k] = make_float2(vr[k], vi[k]);
+      __builtin_amdgcn_sched_barrier(0);   // one row's transform at a time: two interleaved spill
     }
-  }
-  float o_r[F::BL][F::RL], o_i[F::BL][F::RL];
-  F::run(in_r, in_i, o_r, o_i, re, im, twr, twi, tid);
-  // real parts through the LDS tile, then coalesced 16-byte stores
-  __syncthreads();
+    lsfft::lds_barrier();
+    if (bc + (int)gridDim.x < a.BC) {
 #pragma unroll
-  for (int q = 0; q < F::BL; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::RL>(b, m, j);
-    if (F::TOTL % NTB == 0 || b < F::TOTL) {
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r) re[m * XT<N>::SM + j + r * (N / F::RL)] = o_r[q][r];
+      for (int q = 0; q < RPT; ++q) load(bc + gridDim.x, q, wave, lane, in[q]);
     }
-  }
-  __syncthreads();
-  const int nr = (int)((rows - row0) < MP ? (rows - row0) : MP);
-  for (int e = tid; e < nr * N / 4; e += NTB) {
-    const int m = (4 * e) / N, x = (4 * e) - m * N;
-    const float* sp = re + m * XT<N>::SM + x;
-    reinterpret_cast<float4*>(out + row0 * N)[e] = make_float4(sp[0], sp[1], sp[2], sp[3]);
-  }
-}
-
-// y forward: t1[bz][y][kx] -> t2[bz][iy][kx]; pencil g = bz M + kx
-template <int N>
-__global__ __launch_bounds__(NTB) void k_dft_y_fwd(const float2* __restrict__ t1, float2* __restrict__ t2, long long nbz,
-                                                   int M, const float2* __restrict__ twg) {
-  using F = typename ST<N>::template F<-1>;
-  __shared__ float re[N * ST<N>::SN], im[N * ST<N>::SN], twr[N], twi[N];
-  load_tw_split<N>(twr, twi, twg);
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const long long g0 = (long long)blockIdx.x * kPen, npen = nbz * M;
-  float in_r[F::B0][F::R0], in_i[F::B0][F::R0];
+    if (tid < N * M) {
+      const int z = tid / M, kx = tid - z * M;
+      float2* p = L + z * a.PP + kx;
+      float vr[N], vi[N];
 #pragma unroll
-  for (int q = 0; q < F::B0; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::R0>(b, m, j);
-    const long long g = g0 + m;
-    const bool ok = (F::TOT0 % NTB == 0 || b < F::TOT0) && g < npen;
-    const long long bz = ok ? g / M : 0;
-    const int kx = ok ? int(g - bz * M) : 0;
-#pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      float2 v = make_float2(0.0f, 0.0f);
-      if (ok) v = t1[(bz * N + j + r * (N / F::R0)) * M + kx];
-      in_r[q][r] = v.x;
-      in_i[q][r] = v.y;
-    }
-  }
-  float o_r[F::BL][F::RL], o_i[F::BL][F::RL];
-  F::run(in_r, in_i, o_r, o_i, re, im, twr, twi, tid);
-#pragma unroll
-  for (int q = 0; q < F::BL; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::RL>(b, m, j);
-    const long long g = g0 + m;
-    if ((F::TOTL % NTB == 0 || b < F::TOTL) && g < npen) {
-      const long long bz = g / M;
-      const int kx = int(g - bz * M);
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r) {
-        const int iy = kslot<N>(j + r * (N / F::RL), M);
-        if (iy >= 0) t2[(bz * 2 * M + iy) * M + kx] = make_float2(o_r[q][r], o_i[q][r]);
+      for (int y = 0; y < N; ++y) {
+        const float2 v = p[y * a.MP];
+        vr[y] = v.x;
+        vi[y] = v.y;
       }
-    }
-  }
-}
-
-// y inverse: t2[bz][iy][kx] -> t1[bz][y][kx]
-template <int N>
-__global__ __launch_bounds__(NTB) void k_dft_y_inv(const float2* __restrict__ t2, float2* __restrict__ t1, long long nbz,
-                                                   int M, const float2* __restrict__ twg) {
-  using F = typename ST<N>::template F<+1>;
-  __shared__ float re[N * ST<N>::SN], im[N * ST<N>::SN], twr[N], twi[N];
-  load_tw_split<N>(twr, twi, twg);
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const long long g0 = (long long)blockIdx.x * kPen, npen = nbz * M;
-  float in_r[F::B0][F::R0], in_i[F::B0][F::R0];
+      RegFft<N, -1>::run(vr, vi, tw);
 #pragma unroll
-  for (int q = 0; q < F::B0; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::R0>(b, m, j);
-    const long long g = g0 + m;
-    const bool ok = (F::TOT0 % NTB == 0 || b < F::TOT0) && g < npen;
-    const long long bz = ok ? g / M : 0;
-    const int kx = ok ? int(g - bz * M) : 0;
-#pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      const int iy = kslot<N>(j + r * (N / F::R0), M);
-      float2 v = make_float2(0.0f, 0.0f);
-      if (ok && iy >= 0) v = t2[(bz * 2 * M + iy) * M + kx];
-      in_r[q][r] = v.x;
-      in_i[q][r] = v.y;
-    }
-  }
-  float o_r[F::BL][F::RL], o_i[F::BL][F::RL];
-  F::run(in_r, in_i, o_r, o_i, re, im, twr, twi, tid);
-#pragma unroll
-  for (int q = 0; q < F::BL; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::RL>(b, m, j);
-    const long long g = g0 + m;
-    if ((F::TOTL % NTB == 0 || b < F::TOTL) && g < npen) {
-      const long long bz = g / M;
-      const int kx = int(g - bz * M);
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r)
-        t1[(bz * N + j + r * (N / F::RL)) * M + kx] = make_float2(o_r[q][r], o_i[q][r]);
-    }
-  }
-}
-
-// z axis: tiles of kZyx (iy, kx) pairs x kZbc batch-channels, pencil
-// m = yx_local + kZyx bc_local: consecutive lanes read runs of kZyx entries
-// of t2 and write runs of kZbc entries of md
-constexpr int kZyx = 8, kZbc = 8;
-static_assert(kZyx * kZbc == kPen, "z tile");
-
-// z forward: t2[bc][z][yx] -> md[(iz P + yx) BC + bc] * scale(kx)
-template <int N>
-__global__ __launch_bounds__(NTB) void k_dft_z_fwd(const float2* __restrict__ t2, float2* __restrict__ md, int BC, int M,
-                                                   float sc0, float sc1, const float2* __restrict__ twg) {
-  using F = typename ST<N>::template F<-1>;
-  __shared__ float re[N * ST<N>::SN], im[N * ST<N>::SN], twr[N], twi[N];
-  load_tw_split<N>(twr, twi, twg);
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const int P = 2 * M * M;
-  const int nyx = (P + kZyx - 1) / kZyx;
-  const int bc0 = (blockIdx.x / nyx) * kZbc, yx0 = (blockIdx.x % nyx) * kZyx;
-  float in_r[F::B0][F::R0], in_i[F::B0][F::R0];
-#pragma unroll
-  for (int q = 0; q < F::B0; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::R0>(b, m, j);
-    const int yx = yx0 + m % kZyx, bc = bc0 + m / kZyx;
-    const bool ok = (F::TOT0 % NTB == 0 || b < F::TOT0) && yx < P && bc < BC;
-#pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      float2 v = make_float2(0.0f, 0.0f);
-      if (ok) v = t2[((long long)bc * N + j + r * (N / F::R0)) * P + yx];
-      in_r[q][r] = v.x;
-      in_i[q][r] = v.y;
-    }
-  }
-  float o_r[F::BL][F::RL], o_i[F::BL][F::RL];
-  F::run(in_r, in_i, o_r, o_i, re, im, twr, twi, tid);
-#pragma unroll
-  for (int q = 0; q < F::BL; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::RL>(b, m, j);
-    const int yx = yx0 + m % kZyx, bc = bc0 + m / kZyx;
-    if ((F::TOTL % NTB == 0 || b < F::TOTL) && yx < P && bc < BC) {
-      const float sc = (yx % M == 0) ? sc0 : sc1;
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r) {
-        const int iz = kslot<N>(j + r * (N / F::RL), M);
-        if (iz >= 0) md[((long long)iz * P + yx) * BC + bc] = make_float2(o_r[q][r] * sc, o_i[q][r] * sc);
+      for (int y = 0; y < N; ++y) {
+        const int iy = kslot<N>(y, M);
+        if (iy >= 0) p[iy * a.MP] = make_float2(vr[y], vi[y]);
       }
     }
+    lsfft::lds_barrier();
+    if (tid < P) {
+      const int iy = tid / M, kx = tid - iy * M;
+      const float2* p = L + iy * a.MP + kx;
+      float vr[N], vi[N];
+#pragma unroll
+      for (int z = 0; z < N; ++z) {
+        const float2 v = p[z * a.PP];
+        vr[z] = v.x;
+        vi[z] = v.y;
+      }
+      RegFft<N, -1>::run(vr, vi, tw);
+      const float sc = (kx == 0) ? a.s0 : a.s1;
+#pragma unroll
+      for (int z = 0; z < N; ++z) {
+        const int iz = kslot<N>(z, M);
+        if (iz >= 0) md[md_at(iz * P + tid, bc, a.BC)] = make_float2(vr[z] * sc, vi[z] * sc);
+      }
+    }
+    lsfft::lds_barrier();
   }
 }
 
-// z inverse: md -> t2[bc][z][yx]
+// kept modes -> out[x] = sum over kx of c(kx) Re(. e^{+i kx x}), c = s0, s1.
+// The next cube's modes are in flight during the y and x phases.
 template <int N>
-__global__ __launch_bounds__(NTB) void k_dft_z_inv(const float2* __restrict__ md, float2* __restrict__ t2, int BC, int M,
-                                                   const float2* __restrict__ twg) {
-  using F = typename ST<N>::template F<+1>;
-  __shared__ float re[N * ST<N>::SN], im[N * ST<N>::SN], twr[N], twi[N];
-  load_tw_split<N>(twr, twi, twg);
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const int P = 2 * M * M;
-  const int nyx = (P + kZyx - 1) / kZyx;
-  const int bc0 = (blockIdx.x / nyx) * kZbc, yx0 = (blockIdx.x % nyx) * kZyx;
-  float in_r[F::B0][F::R0], in_i[F::B0][F::R0];
+__global__ __launch_bounds__(cube_threads<N>()) void k_cube_inv(const float2* __restrict__ md, float* __restrict__ out,
+                                                                CubeArgs a) {
+  constexpr int NT = cube_threads<N>(), RPT = N * N / NT;
+  extern __shared__ __align__(16) unsigned char smem[];
+  float2* L = reinterpret_cast<float2*>(smem);
+  RegTw<N> tw;
+  tw.load(a.tw);
+  const int tid0 = threadIdx.x, M = a.M, P = 2 * M * M;
+  float zr[N], zi[N];
+  auto load = [&](int bc, int tid) {
 #pragma unroll
-  for (int q = 0; q < F::B0; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::R0>(b, m, j);
-    const int yx = yx0 + m % kZyx, bc = bc0 + m / kZyx;
-    const bool ok = (F::TOT0 % NTB == 0 || b < F::TOT0) && yx < P && bc < BC;
-#pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      const int iz = kslot<N>(j + r * (N / F::R0), M);
+    for (int z = 0; z < N; ++z) {
+      const int iz = kslot<N>(z, M);
       float2 v = make_float2(0.0f, 0.0f);
-      if (ok && iz >= 0) v = md[((long long)iz * P + yx) * BC + bc];
-      in_r[q][r] = v.x;
-      in_i[q][r] = v.y;
+      if (iz >= 0 && tid < P) v = md[md_at(iz * P + tid, bc, a.BC)];
+      zr[z] = v.x;
+      zi[z] = v.y;
     }
-  }
-  float o_r[F::BL][F::RL], o_i[F::BL][F::RL];
-  F::run(in_r, in_i, o_r, o_i, re, im, twr, twi, tid);
+  };
+  int bc = cube_slot(blockIdx.x, gridDim.x);
+  if (bc < a.BC) load(bc, tid0);
+  for (; bc < a.BC; bc += gridDim.x) {
+    int tid = tid0;
+    asm volatile("" : "+v"(tid));
+    if (tid < P) {
+      RegFft<N, 1>::run(zr, zi, tw);
+      const int iy = tid / M, kx = tid - iy * M;
+      float2* p = L + iy * a.MP + kx;
 #pragma unroll
-  for (int q = 0; q < F::BL; ++q) {
-    const int b = tid + q * NTB;
-    int m, j;
-    F::template bj<F::RL>(b, m, j);
-    const int yx = yx0 + m % kZyx, bc = bc0 + m / kZyx;
-    if ((F::TOTL % NTB == 0 || b < F::TOTL) && yx < P && bc < BC) {
-#pragma unroll
-      for (int r = 0; r < F::RL; ++r)
-        t2[((long long)bc * N + j + r * (N / F::RL)) * P + yx] = make_float2(o_r[q][r], o_i[q][r]);
+      for (int z = 0; z < N; ++z) p[z * a.PP] = make_float2(zr[z], zi[z]);
     }
+    lsfft::lds_barrier();
+    if (bc + (int)gridDim.x < a.BC) load(bc + gridDim.x, tid);
+    if (tid < N * M) {
+      const int z = tid / M, kx = tid - z * M;
+      float2* p = L + z * a.PP + kx;
+      float vr[N], vi[N];
+#pragma unroll
+      for (int y = 0; y < N; ++y) {
+        const int iy = kslot<N>(y, M);
+        float2 v = make_float2(0.0f, 0.0f);
+        if (iy >= 0) v = p[iy * a.MP];
+        vr[y] = v.x;
+        vi[y] = v.y;
+      }
+      RegFft<N, 1>::run(vr, vi, tw);
+#pragma unroll
+      for (int y = 0; y < N; ++y) p[y * a.MP] = make_float2(vr[y], vi[y]);
+    }
+    lsfft::lds_barrier();
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+      const int r = tid + q * NT;
+      const float2* src = L + (r / N) * a.PP + (r % N) * a.MP;
+      float vr[N], vi[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        vr[k] = 0.0f;
+        vi[k] = 0.0f;
+        if (k < N / 2 && k < M) {
+          const float2 v = src[k];
+          const float c = (k == 0) ? a.s0 : a.s1;
+          vr[k] = scaled(v.x, c);
+          vi[k] = scaled(v.y, c);
+        }
+      }
+      RegFft<N, 1>::run(vr, vi, tw);
+      if constexpr (N >= 16) {
+        const int r0 = (tid & ~63) + q * NT;          // this wave's first row
+        rows_store<N>(out + ((size_t)bc * N * N + r0) * N, vr, reinterpret_cast<float*>(L + (r0 / N) * a.PP), tid & 63);
+      } else {
+        float4* dst = reinterpret_cast<float4*>(out + ((size_t)bc * N * N + r) * N);
+#pragma unroll
+        for (int k = 0; k < N / 4; ++k) dst[k] = make_float4(vr[4 * k], vr[4 * k + 1], vr[4 * k + 2], vr[4 * k + 3]);
+      }
+    }
+    lsfft::lds_barrier();
   }
 }
 
-static unsigned nblocks(long long work, int per) { return (unsigned)((work + per - 1) / per); }
-
 template <int N>
-static hipError_t dft_fwd_n(int M, int BC, const float* h, float2* t1, float2* t2, float2* md, float sc0, float sc1,
-                            const float2* tw, hipStream_t s) {
-  const long long rows = (long long)BC * N * N;
-  hipLaunchKernelGGL(k_dft_x_fwd<N>, dim3(nblocks(rows, XT<N>::MP)), NTB, 0, s, h, t1, rows, M, tw);
-  const long long nbz = (long long)BC * N;
-  hipLaunchKernelGGL(k_dft_y_fwd<N>, dim3(nblocks(nbz * M, kPen)), NTB, 0, s, t1, t2, nbz, M, tw);
-  const int P = 2 * M * M;
-  const unsigned nz = nblocks(BC, kZbc) * nblocks(P, kZyx);
-  hipLaunchKernelGGL(k_dft_z_fwd<N>, dim3(nz), NTB, 0, s, t2, md, BC, M, sc0, sc1, tw);
+static hipError_t cube_n(bool fwd, int M, int BC, const float* h, const float2* md_in, float2* md_out, float* out,
+                         float s0, float s1, const float2* tw, hipStream_t s) {
+  CubeArgs a{};
+  a.M = M;
+  a.BC = BC;
+  a.MP = M | 1;
+  // a plane holds its rows and its share of a wave's row staging
+  const int need = std::max(N * a.MP, N >= 16 ? kRowStage * N / (64 * 8) : 0);
+  a.PP = need + ((M - need) % 16 + 16) % 16;
+  a.s0 = s0;
+  a.s1 = s1;
+  a.tw = tw;
+  const size_t lds = (size_t)N * a.PP * sizeof(float2);
+  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)(BC < 256 * (N == 32 ? 1 : 4) ? BC : 256 * (N == 32 ? 1 : 4));
+  hipError_t e = fwd ? allow_lds(k_cube_fwd<N>, lds) : allow_lds(k_cube_inv<N>, lds);
+  if (e != hipSuccess) return e;
+  if (fwd) hipLaunchKernelGGL(k_cube_fwd<N>, dim3(grid), cube_threads<N>(), lds, s, h, md_out, a);
+  else hipLaunchKernelGGL(k_cube_inv<N>, dim3(grid), cube_threads<N>(), lds, s, md_in, out, a);
   return hipGetLastError();
 }
 
-template <int N>
-static hipError_t dft_inv_n(int M, int BC, const float2* md, float2* t2, float2* t1, float* out, float c0, float c1,
-                            const float2* tw, hipStream_t s) {
-  const int P = 2 * M * M;
-  const unsigned nz = nblocks(BC, kZbc) * nblocks(P, kZyx);
-  hipLaunchKernelGGL(k_dft_z_inv<N>, dim3(nz), NTB, 0, s, md, t2, BC, M, tw);
-  const long long nbz = (long long)BC * N;
-  hipLaunchKernelGGL(k_dft_y_inv<N>, dim3(nblocks(nbz * M, kPen)), NTB, 0, s, t2, t1, nbz, M, tw);
-  const long long rows = (long long)BC * N * N;
-  hipLaunchKernelGGL(k_dft_x_inv<N>, dim3(nblocks(rows, XT<N>::MP)), NTB, 0, s, t1, out, rows, M, c0, c1, tw);
-  return hipGetLastError();
-}
-
-hipError_t launch_dft_forward(int n, int M, int BC, const float* h, float2* t1, float2* t2, float2* md, float sc0,
-                              float sc1, const float2* tw, hipStream_t s) {
-  if (M < 1 || 2 * M > n) return hipErrorInvalidValue;
+static hipError_t cube(bool fwd, int n, int M, int BC, const float* h, const float2* md_in, float2* md_out,
+                       float* out, float s0, float s1, const float2* tw, hipStream_t s) {
+  if (M < 1 || 2 * M > n || BC < 1) return hipErrorInvalidValue;
   switch (n) {
-    case 8: return dft_fwd_n<8>(M, BC, h, t1, t2, md, sc0, sc1, tw, s);
-    case 16: return dft_fwd_n<16>(M, BC, h, t1, t2, md, sc0, sc1, tw, s);
-    case 32: return dft_fwd_n<32>(M, BC, h, t1, t2, md, sc0, sc1, tw, s);
+    case 8: return cube_n<8>(fwd, M, BC, h, md_in, md_out, out, s0, s1, tw, s);
+    case 16: return cube_n<16>(fwd, M, BC, h, md_in, md_out, out, s0, s1, tw, s);
+    case 32: return cube_n<32>(fwd, M, BC, h, md_in, md_out, out, s0, s1, tw, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_dft_inverse(int n, int M, int BC, const float2* md, float2* t2, float2* t1, float* out, float c0,
-                              float c1, const float2* tw, hipStream_t s) {
-  if (M < 1 || 2 * M > n) return hipErrorInvalidValue;
-  switch (n) {
-    case 8: return dft_inv_n<8>(M, BC, md, t2, t1, out, c0, c1, tw, s);
-    case 16: return dft_inv_n<16>(M, BC, md, t2, t1, out, c0, c1, tw, s);
-    case 32: return dft_inv_n<32>(M, BC, md, t2, t1, out, c0, c1, tw, s);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_dft_forward(int n, int M, int BC, const float* h, float2* md, float sc0, float sc1,
+                              const float2* tw, hipStream_t s) {
+  return cube(true, n, M, BC, h, nullptr, md, nullptr, sc0, sc1, tw, s);
+}
+
+hipError_t launch_dft_inverse(int n, int M, int BC, const float2* md, float* out, float c0, float c1,
+                              const float2* tw, hipStream_t s) {
+  return cube(false, n, M, BC, nullptr, md, nullptr, out, c0, c1, tw, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -41,20 +41,25 @@ struct WgArgs {
 hipError_t launch_wgrad(const WgArgs& a, float* gw, float* gb, hipStream_t s);
 int wgrad_blocks(int B, long long V);
 
-// Per-mode complex products on bf16 MFMA, one wave per mode:
+// The kept modes of a batch are laid out in groups of eight,
+// md[m / 8][bc][m % 8] (bc = 32 sample + channel); mode_slots(nmodes) modes of
+// storage per bc.
+inline long long mode_slots(long long nmodes) { return (nmodes + 7) / 8 * 8; }
+
+// Per-mode complex products on bf16 MFMA (x, g and mode 0 / 1's out as md):
 //  mode 0: out[m][b][o] = sum_i x[m][b][i] r[m][i][o]
 //  mode 1: out[m][b][i] = sum_o x[m][b][o] conj(r[m][i][o])
-//  mode 2: out[m][i][o] (fp32 re,im) = sum_b conj(x[m][b][i]) g[m][b][o]
+//  mode 2: out[m][i][o] (fp32 re,im, mode after mode) = sum_b conj(x[m][b][i]) g[m][b][o]
 hipError_t launch_modemix(int mode, const float2* x, const __hip_bfloat16* r, const float2* g, float* out,
                           int nmodes, int B, hipStream_t s);
 
 // Truncated transforms over [BC][n][n][n] (x fastest), kept modes as above.
-//  forward: modes[m][bc] = scale(kx) * sum_x h e^{-i k.x}, scale = sc0 (kx = 0) or sc1
-//  inverse: out[bc][x] = sum_kept c(kx) Re(modes[m][bc] e^{+i k.x}), c = c0 or c1
-hipError_t launch_dft_forward(int n, int M, int BC, const float* h, float2* t1, float2* t2, float2* modes,
-                              float sc0, float sc1, const float2* tw, hipStream_t s);
-hipError_t launch_dft_inverse(int n, int M, int BC, const float2* modes, float2* t2, float2* t1, float* out,
-                              float c0, float c1, const float2* tw, hipStream_t s);
+//  forward: md = scale(kx) * sum_x h e^{-i k.x}, scale = sc0 (kx = 0) or sc1
+//  inverse: out[bc][x] = sum_kept c(kx) Re(md e^{+i k.x}), c = c0 or c1
+hipError_t launch_dft_forward(int n, int M, int BC, const float* h, float2* md, float sc0, float sc1,
+                              const float2* tw, hipStream_t s);
+hipError_t launch_dft_inverse(int n, int M, int BC, const float2* md, float* out, float c0, float c1,
+                              const float2* tw, hipStream_t s);
 
 // loss = mean_b ||y_b - t_b|| / ||t_b||, dy = (y - t) / (||y_b - t_b|| ||t_b|| B)
 hipError_t launch_loss(const float* y, const float* t, float* dy, int B, long long per_sample, double* part,
