@@ -91,7 +91,7 @@ struct lsfft_fno_s {
   float* h[kMaxLayers + 1] = {nullptr};
   float* pre[kMaxLayers] = {nullptr};
   float2* Hm[kMaxLayers] = {nullptr};
-  float *p1 = nullptr, *z = nullptr, *y = nullptr, *dy = nullptr, *dz = nullptr, *sbuf = nullptr;
+  float *y = nullptr, *dy = nullptr, *sbuf = nullptr;
   float* dbuf[2] = {nullptr, nullptr};
   float2 *ym = nullptr, *gm = nullptr, *tw = nullptr;
   float* wpart = nullptr;
@@ -183,8 +183,9 @@ hipError_t wgrad(lsfft_fno_s* f, const Pw& p, const float* g, const float* h, in
   return launch_wgrad(w, f->grads + p.w_off, f->grads + p.b_off, f->stream);
 }
 
-// forward pass; the output goes to `y`, the tape to the handle's buffers
-hipError_t forward(lsfft_fno_s* f, int B, const float* x, float* y) {
+// forward pass; the output goes to `y`, the layers' inputs and modes to the
+// handle's buffers, with `tape` their pre-activations too
+hipError_t forward(lsfft_fno_s* f, int B, const float* x, float* y, bool tape) {
   const lsfft_fno_arch& a = f->a;
   const int n = a.n, M = a.modes, BC = B * kWidth;
   const float inv_n3 = 1.0f / float(n * n * n);
@@ -203,17 +204,22 @@ hipError_t forward(lsfft_fno_s* f, int B, const float* x, float* y) {
       return e;
     p = pw_args(f, f->L.hid[l], false, f->h[l], B);
     p.add = f->sbuf;
-    p.out = f->pre[l];
+    p.out = tape ? f->pre[l] : nullptr;
     p.out_act = f->h[l + 1];
     if ((e = launch_pointwise(p, f->stream)) != hipSuccess) return e;
   }
-  p = pw_args(f, f->L.proj1, false, f->h[a.layers], B);
-  p.out = f->p1;
-  p.out_act = f->z;
-  if ((e = launch_pointwise(p, f->stream)) != hipSuccess) return e;
-  p = pw_args(f, f->L.proj2, false, f->z, B);
-  p.out = y;
-  return launch_pointwise(p, f->stream);
+  ProjArgs j{};
+  j.h = f->h[a.layers];
+  j.w1 = f->L.proj1.wb;
+  j.w2 = f->L.proj2.wb;
+  j.b1 = f->params + f->L.proj1.b_off;
+  j.b2 = f->params + f->L.proj2.b_off;
+  j.y = y;
+  j.hidden = a.hidden;
+  j.O = a.cout;
+  j.B = B;
+  j.V = f->V;
+  return launch_project(j, f->stream);
 }
 
 // loss and gradients of every parameter into f->grads
@@ -225,18 +231,27 @@ hipError_t backward(lsfft_fno_s* f, int B, const float* x, const float* t) {
   if ((e = launch_loss(f->y, t, f->dy, B, (long long)a.cout * f->V, f->lpart, f->nchunk, f->loss_dev, f->stream)) !=
       hipSuccess)
     return e;
-  // projection
-  if ((e = wgrad(f, f->L.proj2, f->dy, f->z, B)) != hipSuccess) return e;
-  PwArgs p = pw_args(f, f->L.proj2, true, f->dy, B);
-  p.aux = f->p1;
-  p.out = f->dz;
-  if ((e = launch_pointwise(p, f->stream)) != hipSuccess) return e;
-  if ((e = wgrad(f, f->L.proj1, f->dz, f->h[a.layers], B)) != hipSuccess) return e;
   int cur = 0;
-  p = pw_args(f, f->L.proj1, true, f->dz, B);
-  p.aux = f->pre[a.layers - 1];
-  p.out = f->dbuf[cur];
-  if ((e = launch_pointwise(p, f->stream)) != hipSuccess) return e;
+  ProjBwdArgs j{};
+  j.h = f->h[a.layers];
+  j.dy = f->dy;
+  j.pre = f->pre[a.layers - 1];
+  j.w1 = f->L.proj1.wb;
+  j.w1t = f->L.proj1.wbt;
+  j.w2t = f->L.proj2.wbt;
+  j.b1 = f->params + f->L.proj1.b_off;
+  j.out = f->dbuf[cur];
+  j.part1 = f->wpart;
+  j.part2 = f->wpart + (size_t)project_bwd_blocks(B, f->V) * (a.hidden * 33);
+  j.hidden = a.hidden;
+  j.O = a.cout;
+  j.opad16 = f->L.proj2.t_ipad;
+  j.B = B;
+  j.V = f->V;
+  if ((e = launch_project_bwd(j, f->grads + f->L.proj1.w_off, f->grads + f->L.proj1.b_off,
+                              f->grads + f->L.proj2.w_off, f->grads + f->L.proj2.b_off, f->stream)) != hipSuccess)
+    return e;
+  PwArgs p;
   // hidden layers, last to first; dbuf[cur] holds the gradient of pre[l]
   for (int l = a.layers - 1; l >= 0; --l) {
     const float* dpre = f->dbuf[cur];
@@ -298,11 +313,12 @@ lsfft_status lsfft_fno_create(lsfft_fno_t* out, const lsfft_fno_arch* arch, int 
   for (int l = 0; ok && l <= arch->layers; ++l) ok = alloc(f, &f->h[l], B * C * V);
   f->wblk = wgrad_blocks(max_batch, f->V);
   f->nchunk = 64;
-  ok = ok && alloc(f, &f->p1, B * H * V) && alloc(f, &f->z, B * H * V) && alloc(f, &f->dz, B * H * V) &&
-       alloc(f, &f->y, B * (size_t)arch->cout * V) && alloc(f, &f->dy, B * (size_t)arch->cout * V) &&
+  const size_t wpart = std::max((size_t)f->wblk * (32 * 32 + 32),
+                                (size_t)project_bwd_blocks(max_batch, f->V) * (65 * H + 32));
+  ok = ok && alloc(f, &f->y, B * (size_t)arch->cout * V) && alloc(f, &f->dy, B * (size_t)arch->cout * V) &&
        alloc(f, &f->sbuf, B * C * V) && alloc(f, &f->dbuf[0], B * C * V) && alloc(f, &f->dbuf[1], B * C * V) &&
        alloc(f, &f->ym, ns * B * C) && alloc(f, &f->gm, ns * B * C) && alloc(f, &f->tw, (size_t)n) &&
-       alloc(f, &f->wpart, (size_t)f->wblk * (256 * 32 + 256)) &&
+       alloc(f, &f->wpart, wpart) &&
        alloc(f, &f->lpart, B * f->nchunk * 2 + B) && alloc(f, &f->loss_dev, 1);
   if (!ok) {
     release(f);
@@ -347,7 +363,7 @@ lsfft_status lsfft_fno_get_params(lsfft_fno_t f, float* params) {
 
 lsfft_status lsfft_fno_forward(lsfft_fno_t f, int batch, const float* x, float* y) {
   if (!f || !x || !y || batch < 1 || batch > f->max_batch) return LSFFT_E_ARG;
-  FNO_TRY(forward(f, batch, x, y));
+  FNO_TRY(forward(f, batch, x, y, false));
   FNO_TRY(hipStreamSynchronize(f->stream));
   return LSFFT_OK;
 }
@@ -355,7 +371,7 @@ lsfft_status lsfft_fno_forward(lsfft_fno_t f, int batch, const float* x, float* 
 lsfft_status lsfft_fno_loss_grad(lsfft_fno_t f, int batch, const float* x, const float* t, float* grad,
                                  double* loss) {
   if (!f || !x || !t || batch < 1 || batch > f->max_batch) return LSFFT_E_ARG;
-  FNO_TRY(forward(f, batch, x, f->y));
+  FNO_TRY(forward(f, batch, x, f->y, true));
   FNO_TRY(backward(f, batch, x, t));
   if (grad)
     FNO_TRY(hipMemcpyAsync(grad, f->grads, sizeof(float) * f->L.nparam, hipMemcpyDeviceToDevice, f->stream));

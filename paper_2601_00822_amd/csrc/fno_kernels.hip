@@ -28,6 +28,19 @@ __device__ __forceinline__ float gelu_grad(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752440f)) + x * 0.39894228040143267794f * expf(-0.5f * x * x);
 }
 
+// both at once, sharing the error function
+__device__ __forceinline__ void gelu_both(float x, float& z, float& g) {
+  const float e = erff(x * 0.70710678118654752440f);
+  z = 0.5f * x * (1.0f + e);
+  g = 0.5f * (1.0f + e) + x * 0.39894228040143267794f * expf(-0.5f * x * x);
+}
+
+// order the LDS accesses of one wave (no barrier: other waves are not waited for)
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -37,6 +50,13 @@ __device__ __forceinline__ bf16x8 neg8(bf16x8 a) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) r[j] = -a[j];
   return r;
+}
+
+template <typename K>
+static hipError_t allow_lds(K kernel, size_t bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
 }
 
 // ---------------------------------------------------------------------------
@@ -133,7 +153,7 @@ __global__ __launch_bounds__(256) void k_pointwise(PwArgs a) {
 #pragma unroll
           for (int k = 0; k < NT; ++k) val[k] *= gelu_grad(ax[k]);
         }
-        vstore<NT>(a.out + idx, val);
+        if (a.out) vstore<NT>(a.out + idx, val);
         if (a.out_act) {
           float g[NT];
 #pragma unroll
@@ -172,7 +192,9 @@ hipError_t launch_pointwise(const PwArgs& a, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // pointwise weight gradient: MFMA over 16-voxel chunks, per-block partials
 // ---------------------------------------------------------------------------
-constexpr int kWgBlocks = 256;
+// four workgroups to a CU: with one, a wave per SIMD, the loads' latency bound
+// the width's products (94 us per layer at 32^3, batch 32)
+constexpr int kWgBlocks = 1024;
 int wgrad_blocks(int B, long long V) {
   const long long chunks = (long long)B * (V / 16);
   long long nb = (chunks + 3) / 4;
@@ -265,49 +287,364 @@ __global__ __launch_bounds__(256) void k_wgrad(WgArgs a) {
   }
 }
 
-// Fixed-order sum of the per-block partials: a block covers 64 consecutive
-// packed outputs, its four waves sum interleaved quarters of the partials,
-// and the quarters are added in a fixed order.
+// Fixed-order sum of the per-block partials: a workgroup covers 16 consecutive
+// packed outputs, its 16 groups of lanes sum interleaved sixteenths of the
+// partials with eight loads in flight, and the sixteenths are added in order.
+// (64 outputs and quarters, one load at a time, took 24 us.)
 __global__ __launch_bounds__(NTB) void k_wgrad_reduce(const float* __restrict__ part, int nblk, int O, int I,
                                                       int opad, int ipad, float* __restrict__ gw,
                                                       float* __restrict__ gb) {
-  __shared__ float red[4][64];
+  constexpr int U = 8;
+  __shared__ float red[16][17];
   const int n = O * I + O;
-  const int stride = opad * ipad + opad;
-  const int k = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int q = threadIdx.x >> 6;
+  const size_t stride = (size_t)opad * ipad + opad;
+  const int k = blockIdx.x * 16 + (threadIdx.x & 15);
+  const int q = threadIdx.x >> 4;
   float s = 0.0f;
   if (k < n) {
-    const int src = (k < O * I) ? (k / I) * ipad + (k % I) : opad * ipad + (k - O * I);
-    for (int blk = q; blk < nblk; blk += 4) s += part[(size_t)blk * stride + src];
+    const float* src = part + ((k < O * I) ? (k / I) * ipad + (k % I) : opad * ipad + (k - O * I));
+    for (int blk = q; blk < nblk; blk += 16 * U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = (blk + 16 * u < nblk) ? src[(blk + 16 * u) * stride] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) s += v[u];
+    }
   }
-  red[q][threadIdx.x & 63] = s;
+  red[q][threadIdx.x & 15] = s;
   __syncthreads();
   if (q == 0 && k < n) {
-    const float t = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+    float t = 0.0f;
+    for (int r = 0; r < 16; ++r) t += red[r][threadIdx.x];
     if (k < O * I) gw[k] = t;
     else gb[k - O * I] = t;
   }
+}
+
+static hipError_t launch_wgrad_reduce(const float* part, int nblk, int O, int I, int opad, int ipad, float* gw,
+                                      float* gb, hipStream_t s) {
+  const int n = O * I + O;
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + 15) / 16)), NTB, 0, s, part, nblk, O, I, opad, ipad, gw, gb);
+  return hipGetLastError();
 }
 
 hipError_t launch_wgrad(const WgArgs& a, float* gw, float* gb, hipStream_t s) {
   if (a.V % 16 || a.opad % 32 || a.ipad % 32) return hipErrorInvalidValue;
   const dim3 g((unsigned)a.nblk);
   const int to = a.opad / 32, ti = a.ipad / 32;
-  if (to == 1 && ti == 1) hipLaunchKernelGGL((k_wgrad<1, 1>), g, 256, 0, s, a);
-  else if (to == 2 && ti == 1) hipLaunchKernelGGL((k_wgrad<2, 1>), g, 256, 0, s, a);
-  else if (to == 4 && ti == 1) hipLaunchKernelGGL((k_wgrad<4, 1>), g, 256, 0, s, a);
-  else if (to == 8 && ti == 1) hipLaunchKernelGGL((k_wgrad<8, 1>), g, 256, 0, s, a);
-  else if (to == 1 && ti == 2) hipLaunchKernelGGL((k_wgrad<1, 2>), g, 256, 0, s, a);
-  else if (to == 1 && ti == 4) hipLaunchKernelGGL((k_wgrad<1, 4>), g, 256, 0, s, a);
-  else if (to == 1 && ti == 8) hipLaunchKernelGGL((k_wgrad<1, 8>), g, 256, 0, s, a);
-  else return hipErrorInvalidValue;
+  if (to != 1 || ti != 1) return hipErrorInvalidValue;   // the width's layers: lift and hidden
+  hipLaunchKernelGGL((k_wgrad<1, 1>), g, 256, 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int n = a.O * a.I + a.O;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + 63) / 64)), NTB, 0, s, a.part, a.nblk, a.O, a.I,
-                     a.opad, a.ipad, gw, gb);
+  return launch_wgrad_reduce(a.part, a.nblk, a.O, a.I, a.opad, a.ipad, gw, gb, s);
+}
+
+// ---------------------------------------------------------------------------
+// projection: hidden layer of `hidden` channels with GELU, then the output layer
+// ---------------------------------------------------------------------------
+// The accumulator tile of a 32-channel product has rows 8 q + 4 half + 0..3 in
+// a lane's registers 4 q + 0..3; as the B operand of the next product the lane
+// needs rows 16 s + 8 half + 0..7.  Exchanging the upper half-wave's group 2 s
+// with the lower one's group 2 s + 1 gives exactly that, so a hidden tile goes
+// from one product into the next without LDS.
+__device__ __forceinline__ unsigned pack2(float a, float b) {
+  union { unsigned short h[2]; unsigned u; } p;
+  const __bf16 x = (__bf16)a, y = (__bf16)b;
+  p.h[0] = __builtin_bit_cast(unsigned short, x);
+  p.h[1] = __builtin_bit_cast(unsigned short, y);
+  return p.u;
+}
+// B operands s = 0, 1 of a C-layout tile, its entries packed in pairs
+__device__ __forceinline__ void as_operand(const unsigned (&pk)[8], bf16x8 (&op)[2]) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    union { unsigned u[4]; bf16x8 b; } r;
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const auto x = __builtin_amdgcn_permlane32_swap(pk[4 * s + d], pk[4 * s + 2 + d], false, false);
+      r.u[d] = x[0];
+      r.u[2 + d] = x[1];
+    }
+    op[s] = r.b;
+  }
+}
+
+// y = W2 gelu(W1 h + b1) + b2; the hidden activations never leave registers
+// (through HBM they were 1.6 GB per batch of 32 at 32^3 and 128 channels: 364 +
+// 179 us for the two layers, 140 now).  Bound by the error functions: one per
+// hidden channel and voxel.
+__global__ __launch_bounds__(256) void k_project(ProjArgs a) {
+  constexpr int NT = 2;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, col = lane & 31;
+  constexpr int BV = 32 * NT;
+  const long long V = a.V, blocks = (long long)a.B * (V / BV);
+  const bf16x8* w1 = reinterpret_cast<const bf16x8*>(a.w1);
+  const bf16x8* w2 = reinterpret_cast<const bf16x8*>(a.w2);
+  for (long long t = (long long)blockIdx.x * 4 + wave; t < blocks; t += (long long)gridDim.x * 4) {
+    const int b = int(t / (V / BV));
+    const unsigned v = (unsigned)(t % (V / BV)) * BV + NT * col, Vu = (unsigned)V;
+    const float* hb = a.h + (long long)b * 32 * V;
+    float* yb = a.y + (long long)b * a.O * V;
+    bf16x8 bop[2][NT];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float x[NT];
+        vload<NT>(hb + ((s * 16 + half * 8 + j) * Vu + v), x);
+#pragma unroll
+        for (int k = 0; k < NT; ++k) bop[s][k][j] = (__bf16)x[k];
+      }
+    f32x16 acc2[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) acc2[k] = f32x16{0};
+    for (int ot = 0; ot < a.hidden / 32; ++ot) {
+      f32x16 acc[NT];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) acc[k] = f32x16{0};
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const bf16x8 aop = w1[((ot * 32 + col) * 32 + s * 16 + half * 8) / 8];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) acc[k] = mfma(aop, bop[s][k], acc[k]);
+      }
+      unsigned pk[NT][8];
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        const float b0 = a.b1[ot * 32 + 8 * (e / 4) + 4 * half + (e % 4)];
+        const float b1 = a.b1[ot * 32 + 8 * (e / 4) + 4 * half + (e % 4) + 1];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) pk[k][e / 2] = pack2(gelu(acc[k][e] + b0), gelu(acc[k][e + 1] + b1));
+        __builtin_amdgcn_sched_barrier(0);   // few error functions at a time
+      }
+      bf16x8 aop2[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) aop2[s] = w2[(col * a.hidden + (ot * 2 + s) * 16 + half * 8) / 8];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        bf16x8 op[2];
+        as_operand(pk[k], op);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) acc2[k] = mfma(aop2[s], op[s], acc2[k]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int o = 8 * (e / 4) + 4 * half + (e % 4);
+      if (o >= a.O) continue;
+      const float bo = a.b2[o];
+      float val[NT];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) val[k] = acc2[k][e] + bo;
+      vstore<NT>(yb + (o * Vu + v), val);
+    }
+  }
+}
+
+hipError_t launch_project(const ProjArgs& a, hipStream_t s) {
+  if (a.hidden % 32 || a.hidden < 32 || a.O > 32 || a.V % 64) return hipErrorInvalidValue;
+  long long blocks = ((long long)a.B * (a.V / 64) + 3) / 4;
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(k_project, dim3((unsigned)blocks), 256, 0, s, a);
   return hipGetLastError();
+}
+
+// Its backward pass, everything from h and dy: the hidden activations are
+// formed again (the same products and roundings as forward), then per tile of 32
+// voxels
+//   dz = (W2^T dy) gelu'(p), dh = W1^T dz, gW2 += dy z^T, gW1 += dz h^T.
+// Wave w of a workgroup owns hidden channels 32 w .. 32 w + 31: its two weight
+// gradient tiles stay in accumulators over all voxels, with z and dz through a
+// wave-private LDS tile for the products over voxels, and its dz goes to the
+// others as operands through LDS.  dh sums over the hidden channels in their
+// order, so one wave does a voxel tile's whole chain, each wave another tile.
+// One erf and one exp per hidden channel and voxel bound it.  Before, the hidden
+// layer's pre-activations, activations and gradients went through HBM over five
+// kernels (327 + 239 + 230 + 213 us per batch of 32 at 32^3, 128 channels; 530
+// now); with every hidden tile in one wave the accumulators left one wave per
+// SIMD (953 us), without the next tile in flight it took 682.
+constexpr int kPjPitch = 40;                    // bf16 row of an LDS tile
+constexpr int kPjTile = 32 * kPjPitch;
+constexpr int proj_tiles(int W) { return W < 4 ? W : 4; }   // voxel tiles of a workgroup
+template <int W>
+__global__ __launch_bounds__(64 * W, 2) void k_project_bwd(ProjBwdArgs a) {
+  constexpr int NV = proj_tiles(W);
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, col = lane & 31;
+  bf16x8* ops = reinterpret_cast<bf16x8*>(smem);               // [NV][2 W][64]: dz as B operands
+  __bf16* zt = reinterpret_cast<__bf16*>(ops + NV * 2 * W * 64) + wave * 2 * kPjTile;   // [channel][voxel]
+  __bf16* dt = zt + kPjTile;
+  const long long V = a.V, groups = (long long)a.B * (V / 32) / NV;
+  const int kso = a.opad16 / 16;                // k steps over the output channels (1 or 2)
+  const unsigned Vu = (unsigned)V;
+  f32x16 g1 = f32x16{0}, g2 = f32x16{0};
+  float s1[16], s2 = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) s1[e] = 0.0f;
+  // channel rows of a voxel tile, one voxel per lane: the next tile's are in
+  // flight while this one's error functions run
+  float hn[2][8], yn[2][8];
+  auto fetch = [&](long long t) {
+    const int b = int(t / (V / 32));
+    const unsigned v = (unsigned)(t % (V / 32)) * 32 + col;
+    const float* hb = a.h + (long long)b * 32 * V;
+    const float* yb = a.dy + (long long)b * a.O * V;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int c = s * 16 + half * 8 + j;
+        hn[s][j] = hb[c * Vu + v];
+        yn[s][j] = (s < kso && c < a.O) ? yb[c * Vu + v] : 0.0f;
+      }
+  };
+  if ((long long)blockIdx.x < groups) fetch((long long)blockIdx.x * NV);
+  for (long long gr = blockIdx.x; gr < groups; gr += gridDim.x) {
+    const long long t0 = gr * NV;               // V / 32 is a multiple of NV: one sample per group
+    const int b = int(t0 / (V / 32));
+    const unsigned vg = (unsigned)(t0 % (V / 32)) * 32;
+    const float* hb = a.h + (long long)b * 32 * V;
+    const float* yb = a.dy + (long long)b * a.O * V;
+#pragma unroll 1
+    for (int i = 0; i < NV; ++i) {
+      const unsigned v0 = vg + 32 * i;
+      bf16x8 hop[2], yop[2];                    // h and dy as B operands (channel rows, voxel columns)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          hop[s][j] = (__bf16)hn[s][j];
+          yop[s][j] = (__bf16)yn[s][j];
+        }
+      // dy and h as [channel][voxel] rows, for the products over voxels
+      bf16x8 hw[2], yw[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const unsigned vr = v0 + s * 16 + half * 8;
+        const f32x4* hr = reinterpret_cast<const f32x4*>(hb + (col * Vu + vr));
+        const f32x4* yr = reinterpret_cast<const f32x4*>(yb + ((col < a.O ? col : 0) * Vu + vr));
+        const f32x4 h0 = hr[0], h1 = hr[1];
+        f32x4 y0 = yr[0], y1 = yr[1];
+        if (col >= a.O) y0 = y1 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          hw[s][j] = (__bf16)h0[j];
+          hw[s][4 + j] = (__bf16)h1[j];
+          yw[s][j] = (__bf16)y0[j];
+          yw[s][4 + j] = (__bf16)y1[j];
+          if (wave == 0) s2 += y0[j] + y1[j];
+        }
+      }
+      {
+        const long long nt = (i + 1 < NV) ? t0 + i + 1 : (gr + gridDim.x) * NV;
+        if (nt < groups * NV) fetch(nt);
+      }
+      f32x16 p = f32x16{0}, d = f32x16{0};
+      {
+        const bf16x8* w1 = reinterpret_cast<const bf16x8*>(a.w1) + (wave * 32 + col) * 4 + half;
+        const bf16x8* w2t = reinterpret_cast<const bf16x8*>(a.w2t) + (wave * 32 + col) * (2 * kso) + half;
+        p = mfma(w1[0], hop[0], p);
+        p = mfma(w1[2], hop[1], p);
+        d = mfma(w2t[0], yop[0], d);
+        if (kso > 1) d = mfma(w2t[2], yop[1], d);
+      }
+      unsigned pk[8];
+      wave_order();                             // the last tile has been read
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        float dz[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int r = 8 * (e / 4) + 4 * half + (e % 4) + q;
+          float z, gd;
+          gelu_both(p[e + q] + a.b1[wave * 32 + r], z, gd);
+          dz[q] = d[e + q] * gd;
+          zt[r * kPjPitch + col] = (__bf16)z;
+          dt[r * kPjPitch + col] = (__bf16)dz[q];
+          s1[e + q] += dz[q];
+        }
+        pk[e / 2] = pack2(dz[0], dz[1]);
+        __builtin_amdgcn_sched_barrier(0);      // few error functions at a time
+      }
+      bf16x8 op[2];
+      as_operand(pk, op);
+      ops[(i * 2 * W + 2 * wave) * 64 + lane] = op[0];
+      ops[(i * 2 * W + 2 * wave + 1) * 64 + lane] = op[1];
+      wave_order();
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        g2 = mfma(yw[s], *reinterpret_cast<const bf16x8*>(zt + col * kPjPitch + s * 16 + half * 8), g2);   // [o][hidden]
+        g1 = mfma(*reinterpret_cast<const bf16x8*>(dt + col * kPjPitch + s * 16 + half * 8), hw[s], g1);   // [hidden][i]
+      }
+    }
+    lsfft::lds_barrier();
+    if (wave < NV) {
+      const unsigned v = vg + 32 * wave + col;
+      const bf16x8* w1t = reinterpret_cast<const bf16x8*>(a.w1t) + col * (4 * W) + half;
+      f32x16 dh = f32x16{0};
+#pragma unroll
+      for (int s = 0; s < 2 * W; ++s) dh = mfma(w1t[2 * s], ops[(wave * 2 * W + s) * 64 + lane], dh);
+      const float* pb = a.pre + (long long)b * 32 * V;
+      float* ob = a.out + (long long)b * 32 * V;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const unsigned at = (8 * (e / 4) + 4 * half + (e % 4)) * Vu + v;
+        ob[at] = dh[e] * gelu_grad(pb[at]);
+      }
+    }
+    lsfft::lds_barrier();
+  }
+  // this wave's tiles into the block's partial slots; bias gradients summed over
+  // the 32 voxel columns of each half-wave
+  float* part2 = a.part2 + (size_t)blockIdx.x * (32 * a.hidden + 32);
+  float* part1 = a.part1 + (size_t)blockIdx.x * (a.hidden * 32 + a.hidden);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = 8 * (e / 4) + 4 * half + (e % 4);
+    part1[(wave * 32 + r) * 32 + col] = g1[e];
+    part2[r * a.hidden + wave * 32 + col] = g2[e];
+    float t = s1[e];
+#pragma unroll
+    for (int m = 16; m > 0; m >>= 1) t += __shfl_xor(t, m, 64);
+    if (col == 0) part1[a.hidden * 32 + wave * 32 + r] = t;
+  }
+  if (wave == 0) {
+    s2 += __shfl_xor(s2, 32, 64);
+    if (half == 0) part2[32 * a.hidden + col] = s2;
+  }
+}
+
+int project_bwd_blocks(int B, long long V) {
+  const long long nb = (long long)B * (V / 32) / 4;
+  return (int)(nb < 512 ? (nb < 1 ? 1 : nb) : 512);
+}
+
+template <int W>
+static hipError_t project_bwd(const ProjBwdArgs& a, int nblk, hipStream_t s) {
+  constexpr size_t lds = (size_t)proj_tiles(W) * 2 * W * 64 * 16 + (size_t)W * 2 * kPjTile * 2;
+  const hipError_t e = allow_lds(k_project_bwd<W>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_project_bwd<W>, dim3(nblk), 64 * W, lds, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_project_bwd(const ProjBwdArgs& a, float* gw1, float* gb1, float* gw2, float* gb2, hipStream_t s) {
+  if (a.V % 128 || a.O > 32) return hipErrorInvalidValue;
+  const int nblk = project_bwd_blocks(a.B, a.V);
+  hipError_t e;
+  switch (a.hidden) {
+    case 32: e = project_bwd<1>(a, nblk, s); break;
+    case 64: e = project_bwd<2>(a, nblk, s); break;
+    case 128: e = project_bwd<4>(a, nblk, s); break;
+    case 256: e = project_bwd<8>(a, nblk, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  if (e != hipSuccess) return e;
+  e = launch_wgrad_reduce(a.part2, nblk, a.O, a.hidden, 32, a.hidden, gw2, gb2, s);
+  if (e != hipSuccess) return e;
+  return launch_wgrad_reduce(a.part1, nblk, a.hidden, 32, a.hidden, 32, gw1, gb1, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -493,13 +830,6 @@ __global__ __launch_bounds__(256) void k_modemix(const float2* __restrict__ x, c
   }
 }
 
-template <typename K>
-static hipError_t allow_lds(K kernel, size_t bytes) {
-  if (bytes <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
-}
-
 hipError_t launch_modemix(int mode, const float2* x, const __hip_bfloat16* r, const float2* g, float* out,
                           int nmodes, int B, hipStream_t s) {
   const dim3 grid((unsigned)((nmodes + kMg - 1) / kMg));
@@ -643,10 +973,6 @@ __device__ __forceinline__ int cube_slot(int b, int G) {
 // straight from HBM touches 64 lines per access and keeps 64 KB of them open,
 // twice the L1 (the inverse took 72 us per batch of 32 at N = 32 that way).
 constexpr int kRowPitch = 20, kRowStage = 64 * kRowPitch * 4;   // words, bytes per wave
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 template <int N>
 __device__ __forceinline__ void rows_fetch(const float* __restrict__ src, f32x4 (&v)[N / 4], int lane) {
   // piece i of 16 entries: rows (i % 4) * 16 + lane / 4, entries 16 (i / 4) + 4 (lane % 4)

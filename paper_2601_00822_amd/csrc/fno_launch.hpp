@@ -11,7 +11,7 @@ constexpr int kWidth = 32;   // channels of the hidden layers (one MFMA tile)
 
 // Pointwise layer out[b][o][v] = sum_i w[o][i] in[b][i][v] (+ bias[o])
 // (+ add[b][o][v]); then, if aux, out *= GELU'(aux[b][o][v]); if out_act,
-// out_act = GELU(out).  w is bf16 [opad][ipad], zero padded (opad multiple of
+// out_act = GELU(out).  out may be null when only out_act is wanted.  w is bf16 [opad][ipad], zero padded (opad multiple of
 // 32, ipad multiple of 16).
 struct PwArgs {
   const float* in;
@@ -40,6 +40,34 @@ struct WgArgs {
 };
 hipError_t launch_wgrad(const WgArgs& a, float* gw, float* gb, hipStream_t s);
 int wgrad_blocks(int B, long long V);
+
+// Projection y = W2 gelu(W1 h + b1) + b2 of h [B][32][V]: w1 bf16
+// [hidden][32], w2 bf16 [32][hidden] (rows beyond O zero).
+struct ProjArgs {
+  const float* h;
+  const __hip_bfloat16 *w1, *w2;
+  const float *b1, *b2;
+  float* y;
+  int hidden, O, B;
+  long long V;
+};
+hipError_t launch_project(const ProjArgs& a, hipStream_t s);
+
+// Its backward pass: out [B][32][V] = (W1^T dz) gelu'(pre), dz = (W2^T dy)
+// gelu'(W1 h + b1), and the packed gradients of both layers.  w1t bf16
+// [32][hidden], w2t bf16 [hidden][opad16]; part1, part2: partial sums of
+// project_bwd_blocks workgroups, hidden 32 + hidden and 32 hidden + 32 floats
+// each.  hidden 32, 64, 128 or 256 (hipErrorInvalidValue otherwise).
+struct ProjBwdArgs {
+  const float *h, *dy, *pre;
+  const __hip_bfloat16 *w1, *w1t, *w2t;
+  const float* b1;
+  float *out, *part1, *part2;
+  int hidden, O, opad16, B;
+  long long V;
+};
+int project_bwd_blocks(int B, long long V);
+hipError_t launch_project_bwd(const ProjBwdArgs& a, float* gw1, float* gb1, float* gw2, float* gb2, hipStream_t s);
 
 // The kept modes of a batch are laid out in groups of eight,
 // md[m / 8][bc][m % 8] (bc = 32 sample + channel); mode_slots(nmodes) modes of
