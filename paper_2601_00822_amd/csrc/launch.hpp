@@ -78,6 +78,11 @@ hipError_t launch_xpass(bool f64, const LaunchArgs& a, int mode, int dim, int le
 hipError_t launch_ypass(bool f64, const LaunchArgs& a, int dir, int which, int ncomp, int gate, int len, int var);
 hipError_t launch_green(bool f64, const LaunchArgs& a, int mode, int dim, int len, int var);
 hipError_t launch_cg_update(bool f64, const LaunchArgs& a);
+// Basic-scheme iterations of `count` 2D solves (device list inst), one workgroup
+// each, until they stop or for `steps` iterations (k_solve2d.hip); a.lds is the
+// largest solve2d_lds among them (0: the grid does not fit).
+size_t solve2d_lds(bool f64, int nx, int ny, int nphase);
+hipError_t launch_solve2d(bool f64, const LaunchArgs& a, const int* inst, int count, int steps);
 hipError_t launch_reduce(const LaunchArgs& a, const int* inst_list, const int* d_ninst, int ninst, int mode);
 hipError_t launch_phase_max(const uint8_t* phase, long long n, int* out, hipStream_t s);
 hipError_t launch_accumulate(bool f64, int dim, const LaunchArgs& a, const GroupDesc* groups, int g, long long nvox);

@@ -25,6 +25,7 @@ using namespace lsfft;
 namespace {
 
 constexpr int kMaxGrid = 4096;  // blocks of a persistent launch
+constexpr int kSolve2dSteps = 512;   // iterations of one k_solve2d launch at most
 
 bool supported_len(int64_t n) {
   for (int i = 0; i < kNumLens; ++i)
@@ -865,6 +866,21 @@ lsfft_status read_states(Batch& b, std::vector<int>& running) {
   return LSFFT_OK;
 }
 
+// LDS bytes of the one-workgroup-per-solve kernel when every solve of the batch
+// can take it (2D, basic scheme, up to 4096 points: above, a solve's launches are
+// faster than one CU, see k_solve2d.hip), else 0.
+size_t fits_solve2d(const Batch& b) {
+  if (b.p->scheme != LSFFT_BASIC) return 0;
+  size_t lds = 0;
+  for (size_t i = 0; i < b.specs.size(); ++i) {
+    const Geometry& g = b.geo[i];
+    const size_t need = g.dim == 2 ? solve2d_lds(b.p->f64, g.nx, g.ny, b.specs[i].tab->nphase) : 0;
+    if (need == 0) return 0;
+    lds = std::max(lds, need);
+  }
+  return lds;
+}
+
 // Iterate every solve on the dynamic lists until none is running.  With
 // `max_rounds` > 0 at most that many single-iteration rounds are run, without
 // a graph (the mixed-precision outer step).
@@ -873,6 +889,23 @@ lsfft_status iterate(Batch& b, int max_rounds = 0, std::vector<int>* running_out
   const bool cg = p->scheme == LSFFT_CG || p->scheme == LSFFT_CG_PLAIN;
   hipStream_t st = p->stream;
   const bool timing = (p->flags & LSFFT_TIMING) != 0 || p->force_timing;
+  // timed plans keep one launch per pass, which is what they time
+  if (const size_t lds = timing ? 0 : fits_solve2d(b)) {
+    p->timing_active = false;
+    std::vector<int> running;
+    const int steps = max_rounds > 0 ? max_rounds : kSolve2dSteps;
+    do {
+      LaunchArgs a = base_args(b);
+      a.lds = lds;
+      LSFFT_TRY(launch_solve2d(p->f64, a, b.d_inst, b.n_running, steps));
+      lsfft_status ls = read_states(b, running);
+      if (ls != LSFFT_OK) return ls;
+      if ((int)running.size() < b.n_running && !running.empty() && (ls = upload_lists(b, running, false)) != LSFFT_OK)
+        return ls;
+    } while (max_rounds == 0 && !running.empty());
+    if (running_out) *running_out = running;
+    return LSFFT_OK;
+  }
   p->timing_active = timing;
   if (cg) {
     // r0 = P f - A u^b from one operator application on u^b
