@@ -19,7 +19,7 @@ struct LaunchArgs {
   const double* lame;     // device Lame table, pairs (lambda, mu)
   const void* tw;         // device twiddle table in the plan precision
   hipEvent_t ev0 = nullptr, ev1 = nullptr;   // if set: timestamps of the kernel's own start and end
-  // y pass only: solves whose stopping rule the launch applies first (device
+  // first y pass or plane pass: solves whose stopping rule the launch applies first (device
   // list and device count), or null
   const int* red_inst = nullptr;
   const int* red_n = nullptr;
@@ -76,6 +76,11 @@ int schedule_variants(bool f64, int dim, int kind, int len);
 // dispatch on (precision, dimension, transform length, schedule variant)
 hipError_t launch_xpass(bool f64, const LaunchArgs& a, int mode, int dim, int len, int var);
 hipError_t launch_ypass(bool f64, const LaunchArgs& a, int dir, int which, int ncomp, int gate, int len, int var);
+// Inverse y, x with Hooke's law and forward y of whole FP32 planes (k_plane.hip);
+// items are (normal or shear strains, plane).  plane_lds: LDS bytes, 0 for grids that
+// keep the three passes.
+size_t plane_lds(bool f64, int nx, int ny, int nz);
+hipError_t launch_plane(const LaunchArgs& a, int nx, int ny);
 hipError_t launch_green(bool f64, const LaunchArgs& a, int mode, int dim, int len, int var);
 hipError_t launch_cg_update(bool f64, const LaunchArgs& a);
 // Basic-scheme iterations of `count` 2D solves (device list inst), one workgroup

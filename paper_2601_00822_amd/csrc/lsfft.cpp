@@ -104,7 +104,7 @@ struct BatchGroup {
   int first = 0, count = 0;
 };
 
-enum ListId { L_XLEAD, L_YLEAD, L_GLEAD, L_X, L_Y, L_G, L_CG, L_XALL, L_YALL, L_GALL, L_NUM };
+enum ListId { L_XLEAD, L_YLEAD, L_GLEAD, L_X, L_Y, L_P, L_G, L_CG, L_XALL, L_YALL, L_GALL, L_NUM };
 
 // A contiguous run of work items of one list that share the kernel
 // specialization (dimension and transform length) and therefore one launch.
@@ -214,6 +214,7 @@ struct Geometry {
   int blk;                              // kx-blocked spectra between the y and outer passes
   int bls;                              // blocked: entries from one y line of a block to the next (8 nz)
   size_t lds_x, lds_xi, lds_y, lds_g;   // lds_xi: x pass of the iteration
+  size_t lds_p;                         // planes in one pass (0: the y, x and y passes)
 };
 
 // the kx-blocked layout needs a 3D grid with nx a multiple of 16
@@ -267,6 +268,7 @@ bool geometry(bool f64, const lsfft_grid& g, const int sched[3][kNumLens], Geome
   o->lds_x = query_geometry(f64, 0, o->nx, o->var_x, &mr);
   o->lds_xi = query_geometry(f64, 3, o->nx, o->var_x, nullptr);
   o->lds_y = (g.dim == 3) ? query_geometry(f64, 1, o->ny, o->var_y, &mpy) : 0;
+  o->lds_p = g.dim == 3 ? plane_lds(f64, o->nx, o->ny, o->nz) : 0;
   o->lds_g = query_geometry(f64, 2, outer, o->var_g, &mpg);
   if (!o->lds_x || !o->lds_xi || !o->lds_g || (g.dim == 3 && !o->lds_y)) return false;
   const int rows = o->ny * o->nz;
@@ -364,6 +366,7 @@ struct Batch {
   std::vector<Seg> segs[L_NUM];   // per list: one segment per (dim, transform length)
   int nseg_total = 0;
   int n_running = 0;
+  bool plane = false;   // iterate eligible solves with k_plane in place of the y, x and y passes
   double tol = 1e-8;
   int max_iter = 0;
   bool averaging = false;
@@ -445,18 +448,22 @@ LaunchArgs base_args(Batch& b) {
 void list_key(const Batch& b, int l, int i, int* dim, int* len, int* items, size_t* lds, int* var) {
   const Geometry& g = b.geo[i];
   *dim = g.dim;
+  const size_t plane = b.plane ? g.lds_p : 0;
   switch (l) {
-    case L_X: *len = g.nx; *items = g.items_x; *lds = g.lds_xi; *var = g.var_x; break;
+    case L_X: *len = g.nx; *items = plane ? 0 : g.items_x; *lds = g.lds_xi; *var = g.var_x; break;
+    // one key for the two lengths; two work items (normal strains, shears) per plane
+    case L_P: *len = g.nx << 16 | g.ny; *items = plane ? 2 * g.nz : 0; *lds = plane; *var = 0; break;
+    case L_Y: *len = g.ny; *items = plane ? 0 : g.items_y; *lds = g.lds_y; *var = g.var_y; break;
     case L_XALL: *len = g.nx; *items = g.items_xall; *lds = g.lds_x; *var = g.var_x; break;
     case L_XLEAD: *len = g.nx; *items = g.items_xft; *lds = g.lds_x; *var = g.var_x; break;
-    case L_Y: case L_YALL: case L_YLEAD: *len = g.ny; *items = g.items_y; *lds = g.lds_y; *var = g.var_y; break;
+    case L_YALL: case L_YLEAD: *len = g.ny; *items = g.items_y; *lds = g.lds_y; *var = g.var_y; break;
     case L_G: case L_GALL: case L_GLEAD:
       *len = (g.dim == 3) ? g.nz : g.ny; *items = g.items_g; *lds = g.lds_g; *var = g.var_g; break;
     default: *len = 0; *items = g.items_cg; *lds = 0; *var = 0; break;   // L_CG
   }
 }
 
-bool is_dynamic(int l) { return l == L_X || l == L_Y || l == L_G || l == L_CG; }
+bool is_dynamic(int l) { return l == L_X || l == L_Y || l == L_P || l == L_G || l == L_CG; }
 
 // Lay out every list as segments (first call), then fill the dynamic lists
 // with the items of the running solves (every call) and upload lists and
@@ -580,6 +587,9 @@ lsfft_status prepare(Batch& b, bool validate = true) {
   const bool cg = p->scheme == LSFFT_CG || p->scheme == LSFFT_CG_PLAIN;
 
   if (host_fence(p) != LSFFT_OK) return LSFFT_E_DEVICE;
+  // timed plans and autotuning keep one launch per pass, which is what they time
+  // (the iterates are the same bit for bit)
+  b.plane = (p->flags & LSFFT_TIMING) == 0 && !p->force_timing;
   // geometry, Lame tables
   b.geo.resize(n);
   b.desc.assign(n, InstDesc{});
@@ -631,6 +641,7 @@ lsfft_status prepare(Batch& b, bool validate = true) {
     const Geometry& g = b.geo[i];
     list_need[L_X] += g.items_x; list_need[L_Y] += g.items_y; list_need[L_G] += g.items_g;
     list_need[L_CG] += g.items_cg;
+    if (b.plane && g.lds_p) list_need[L_P] += 2 * g.nz;
   }
   if (list_need[L_X] == 0) list_need[L_X] = 1;
   list_need[L_XALL] = list_need[L_XLEAD] = 0;
@@ -799,6 +810,25 @@ hipError_t pass_y(Batch& b, int list, int dir, int which, int ncomp, int gate, i
   if (reduce) return pass_reduce(b, M_ITER);
   return hipSuccess;
 }
+// The strain spectra's way to the stress spectra: inverse y, x with Hooke's law,
+// forward y; one launch per plane size for the solves that k_plane takes.
+hipError_t pass_yxy(Batch& b, bool reduce) {
+  for (const Seg& sg : b.segs[L_P]) {
+    if (sg.count == 0) continue;
+    LaunchArgs a = largs(b, L_P, sg);
+    if (reduce) {
+      a.red_inst = b.d_inst;
+      a.red_n = b.d_counts + kMaxSegs - 1;
+      reduce = false;
+    }
+    const hipError_t e = launch_plane(a, sg.len >> 16, sg.len & 0xffff);
+    if (e != hipSuccess) return e;
+  }
+  hipError_t e = pass_y(b, L_Y, +1, 0, 6, 1, LSFFT_K_YPASS, reduce);
+  if (e == hipSuccess) e = pass_x(b, L_X, M_ITER, LSFFT_K_XPASS);
+  if (e == hipSuccess) e = pass_y(b, L_Y, -1, 0, 6, 1, LSFFT_K_YPASS);
+  return e;
+}
 hipError_t pass_g(Batch& b, int list, int mode, int cls) {
   for (const Seg& sg : b.segs[list]) {
     if (sg.count == 0) continue;
@@ -909,15 +939,13 @@ lsfft_status iterate(Batch& b, int max_rounds = 0, std::vector<int>* running_out
   p->timing_active = timing;
   if (cg) {
     // r0 = P f - A u^b from one operator application on u^b
-    LSFFT_TRY(pass_y(b, L_Y, +1, 0, 6, 1, LSFFT_K_YPASS));
-    LSFFT_TRY(pass_x(b, L_X, M_ITER, LSFFT_K_XPASS));
-    LSFFT_TRY(pass_y(b, L_Y, -1, 0, 6, 1, LSFFT_K_YPASS));
+    LSFFT_TRY(pass_yxy(b, false));
     LSFFT_TRY(pass_g(b, L_G, M_CG_INIT, LSFFT_K_GREEN));
     LSFFT_TRY(pass_reduce(b, M_CG_INIT));
   }
   const int per_round = max_rounds > 0 ? 1 : p->poll;
   // Inside a round of the basic scheme the stopping rule of iteration k runs
-  // at the start of iteration k + 1's first y pass (same block size and
+  // at the start of iteration k + 1's first y or plane pass (same block size and
   // summation order as k_reduce, so the same bits); the round's last
   // iteration keeps k_reduce, since the host reads the states after it.
   // Timed plans keep k_reduce throughout, so that each pass class is timed
@@ -929,10 +957,8 @@ lsfft_status iterate(Batch& b, int max_rounds = 0, std::vector<int>* running_out
     bool pending = false;
     for (int k = 0; k < per_round; ++k) {
       hipError_t e;
-      if ((e = pass_y(b, L_Y, +1, 0, 6, 1, LSFFT_K_YPASS, pending)) != hipSuccess) return e;
+      if ((e = pass_yxy(b, pending)) != hipSuccess) return e;
       pending = false;
-      if ((e = pass_x(b, L_X, M_ITER, LSFFT_K_XPASS)) != hipSuccess) return e;
-      if ((e = pass_y(b, L_Y, -1, 0, 6, 1, LSFFT_K_YPASS)) != hipSuccess) return e;
       if (aa) {
         if ((e = pass_g(b, L_G, M_AA_RES, LSFFT_K_GREEN)) != hipSuccess) return e;
         if ((e = pass_reduce(b, M_AA_RES)) != hipSuccess) return e;

@@ -1,0 +1,113 @@
+"""FP32 grids whose planes are transformed in one pass: iterates against the FP64
+oracle and, bit for bit, against the three passes (which timed plans keep) at every
+pair of plane lengths, on both spectral layouts, with shifted microstructures and in
+a batch with grids that keep the three passes.
+
+Bars: relative strain error 1e-5 (FP32 against the FP64 iterate), the same iteration
+count, residual within 1e-4 of the oracle's.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import lsfft_oracle as O
+import gen
+
+pytestmark = pytest.mark.gpu
+
+LAME3 = np.array([[1.0, 1.0], [4.0, 2.0], [0.5, 3.0]])
+LENS = (32, 48, 64, 96, 128)
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def say(msg):
+    print(f"\n[case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+def problem(shape, seed):
+    rng = np.random.default_rng(seed)
+    phase = rng.integers(0, len(LAME3), size=shape).astype(np.uint8)
+    return phase, rng.normal(size=(3,) + tuple(shape)).astype(np.float32)
+
+
+# the fewest planes with which the lengths take this path
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("ny", LENS)
+@pytest.mark.parametrize("nx", LENS)
+def test_iterates(dev, nx, ny, layout):
+    import torch
+    from paper_2601_00822_amd import Plan
+    nz = 4 if nx * ny <= 4096 else 16 if nx * ny <= 9216 else 96
+    if nz == 96 and layout == 0:
+        pytest.skip("rows: covered by the smaller planes")
+    shape = (nz, ny, nx)
+    say(f"{shape} layout {layout}")
+    phase, f = problem(shape, nx + ny)
+    plan = Plan([shape], prec="f32", scheme="basic")
+    plan.set_schedule("layout", 0, layout)
+    k = 2 if nz == 96 else 4
+    ref = O.solve_basic(phase, LAME3, f.astype(np.float64), tol=1e-12, max_iter=k)
+    out, rep = plan.solve(torch.from_numpy(phase).to(dev), LAME3, torch.from_numpy(f).to(dev), tol=1e-12, max_iter=k)
+    timed = Plan([shape], prec="f32", scheme="basic", timing=True)
+    timed.set_schedule("layout", 0, layout)
+    out3, rep3 = timed.solve(torch.from_numpy(phase).to(dev), LAME3, torch.from_numpy(f).to(dev), tol=1e-12, max_iter=k)
+    torch.cuda.synchronize()
+    plan.close()
+    timed.close()
+    assert rep.residual == rep3.residual
+    for name in out:
+        assert torch.equal(out[name], out3[name]), name
+    assert rep.iters == ref.iters
+    assert abs(rep.residual - ref.residual) <= 1e-4 * ref.residual
+    assert O.relative_strain_error_voigt(out["eps"].double().cpu().numpy(), O.to_voigt(ref.eps)) <= 1e-5
+
+
+def test_shifts_and_mixed_batch(dev):
+    # one grid on this path, one on the three passes, in one averaging call; the
+    # shifts move the maps by odd steps along every axis
+    import torch
+    from paper_2601_00822_amd import Plan
+    shapes = [(8, 32, 48), (8, 16, 32)]
+    shifts = np.array([[0, 0, 0], [1, 5, 3], [7, 31, 47], [2, 9, 16]], dtype=np.int32)
+    groups, refs = [], []
+    for g, shp in enumerate(shapes):
+        phase, f = problem(shp, 11 + g)
+        sh = shifts % np.array(shp)
+        groups.append(dict(grid=g, phase=torch.from_numpy(phase).to(dev), lame=LAME3, f=torch.from_numpy(f).to(dev),
+                           shifts=sh))
+        refs.append(O.translate_average(phase, LAME3, f.astype(np.float64), sh, tol=1e-8)[0])
+    say(f"averages over {len(shifts)} shifts of {shapes}")
+    plan = Plan(shapes, prec="f32", max_batch=8, refine=True)
+    avgs, _, st = plan.translate_average_batch(groups, tol=1e-8)
+    torch.cuda.synchronize()
+    plan.close()
+    assert st == 0
+    for a, ref in zip(avgs, refs):
+        a = a.cpu().numpy()
+        # both stop at residual 1e-8
+        assert O.relative_strain_error_voigt(a[6:12], ref[6:12]) <= 1e-5
+
+
+@pytest.mark.parametrize("scheme", ["cg", "anderson"])
+def test_schemes(dev, scheme):
+    import torch
+    from paper_2601_00822_amd import Plan
+    shape = (16, 48, 64)
+    phase, f = problem(shape, 5)
+    say(f"{shape} {scheme}, refined to 1e-8")
+    ref = O.solve_basic(phase, LAME3, f.astype(np.float64), tol=1e-10)
+    plan = Plan([shape], prec="f32", scheme=scheme, refine=True)
+    out, rep = plan.solve(torch.from_numpy(phase).to(dev), LAME3, torch.from_numpy(f).to(dev), tol=1e-8)
+    torch.cuda.synchronize()
+    plan.close()
+    assert rep.status == 0
+    assert O.relative_strain_error_voigt(out["eps"].double().cpu().numpy(), O.to_voigt(ref.eps)) <= 1e-5
