@@ -121,15 +121,17 @@ hipError_t launch_phase_max(const uint8_t* phase, long long n, int* out, hipStre
 }
 
 hipError_t launch_accumulate(bool f64, int dim, const LaunchArgs& a, const GroupDesc* groups, int g, long long nvox) {
-  long long blocks = (nvox + NTR - 1) / NTR;
+  // a wave per workgroup where more would leave CUs idle
+  const int nth = nvox < 256 * NTR ? 64 : NTR;
+  long long blocks = (nvox + nth - 1) / nth;
   if (blocks > 4096) blocks = 4096;
   const dim3 grid((unsigned)blocks);
   if (f64) {
-    if (dim == 3) hipLaunchKernelGGL((k_accumulate<double, 3>), grid, NTR, 0, a.stream, a.desc, groups, g, a.lame);
-    else hipLaunchKernelGGL((k_accumulate<double, 2>), grid, NTR, 0, a.stream, a.desc, groups, g, a.lame);
+    if (dim == 3) hipLaunchKernelGGL((k_accumulate<double, 3>), grid, nth, 0, a.stream, a.desc, groups, g, a.lame);
+    else hipLaunchKernelGGL((k_accumulate<double, 2>), grid, nth, 0, a.stream, a.desc, groups, g, a.lame);
   } else {
-    if (dim == 3) hipLaunchKernelGGL((k_accumulate<float, 3>), grid, NTR, 0, a.stream, a.desc, groups, g, a.lame);
-    else hipLaunchKernelGGL((k_accumulate<float, 2>), grid, NTR, 0, a.stream, a.desc, groups, g, a.lame);
+    if (dim == 3) hipLaunchKernelGGL((k_accumulate<float, 3>), grid, nth, 0, a.stream, a.desc, groups, g, a.lame);
+    else hipLaunchKernelGGL((k_accumulate<float, 2>), grid, nth, 0, a.stream, a.desc, groups, g, a.lame);
   }
   return hipGetLastError();
 }
