@@ -1645,6 +1645,24 @@ __device__ void green_item(const InstDesc& D, InstState* __restrict__ St, int lo
       pk0[q] = t.kx(m) == 0;
       pth[q] = t.other(m);
     }
+    if (t.kx0 != 0) {
+      // without the column: no branch between the points' loads, which are then in
+      // flight together (outside the grid the force is zero)
+      inverse_all(SS, 0, std::integral_constant<int, S>{}, [&](int c, int q, int r, T& re, T& im) {
+        re = T(0);
+        im = T(0);
+        const int g = pv[q] ? gidx(q, r) : 0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          const typename C2<T>::type kv = ldc<T>(cptr<T>(D.Kh, Pc, c * DIM + j), g);
+          re += kv.x * vr[j][q][r] - kv.y * vi[j][q][r];
+          im += kv.x * vi[j][q][r] + kv.y * vr[j][q][r];
+        }
+        re *= inv_n;
+        im *= inv_n;
+      });
+      return;
+    }
     inverse_all(SS, 0, std::integral_constant<int, S>{}, [&](int c, int q, int r, T& re, T& im) {
       re = T(0);
       im = T(0);
@@ -2121,7 +2139,16 @@ __global__ __launch_bounds__((GSched<T, NG, V>::NTH)) __attribute__((amdgpu_wave
   extern __shared__ __align__(16) unsigned char smem[];
   const int n_items = *nitems;
   for (int w = xcd_slot(blockIdx.x, gridDim.x); w < n_items; w += gridDim.x) {
-    const WorkItem it = items[w];
+    int e = w;
+    if constexpr (MODE == M_KCONV) {
+      // the solves' shares of one tile run together, so that the tile of the
+      // kernel spectrum (s d components, six times a force's) comes from the L2
+      // of their XCD after the first: 277 us for 32 forces on 64^3 in FP64 where
+      // solve after solve took 353
+      const int per = descs[items[0].inst].items_g, ni = n_items / per;
+      if (per * ni == n_items) e = (w % ni) * per + w / ni;
+    }
+    const WorkItem it = items[e];
     const InstDesc& D = descs[it.inst];
     InstState* St = states + it.inst;
     if (gated(MODE) && St->status != ST_RUNNING) continue;
