@@ -92,12 +92,22 @@ __device__ __forceinline__ void vstore(float* p, const float (&v)[NT]) {
   *reinterpret_cast<typename VecF<NT>::type*>(p) = x;
 }
 
-template <int KS, int NT>
-__global__ __launch_bounds__(256) void k_pointwise(PwArgs a) {
+// HBM bounds it.  The rows that are added (ADD) and the pre-activations (AUX) are
+// loaded eight at a time, the first before the products and the others one batch
+// ahead of the stores.  One row's load at a time between the stores took 135 us for
+// a forward layer of 32^3, batch 32 (403 MB), and 151 us for a backward one (537
+// MB); this takes 95 (4.3 TB/s) and 110 us (4.9 TB/s).  For width 32, two voxels per
+// lane and three waves per SIMD (with both kinds of rows two, the third spills: 142
+// us): with four voxels one wave fits, 125 and 138 us.
+template <int KS, int NT, bool ADD, bool AUX>
+__global__ __launch_bounds__(256, (KS == 2 && !(ADD && AUX)) || (KS == 1 && !ADD && !AUX) ? 3 : 1) void k_pointwise(
+    PwArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;
   constexpr int BV = 32 * NT;   // voxels per wave block
+  constexpr int GE = 8, NG = 16 / GE;   // rows loaded together
+  typedef float VN __attribute__((ext_vector_type(NT)));
   const long long V = a.V;
   const long long blocks = (long long)a.B * (V / BV);
   const bf16x8* w8 = reinterpret_cast<const bf16x8*>(a.w);
@@ -119,6 +129,19 @@ __global__ __launch_bounds__(256) void k_pointwise(PwArgs a) {
       }
     }
     for (int ot = 0; ot < a.opad / 32; ++ot) {
+      // row of accumulator entry e; rows past the last one load the last one
+      auto row = [&](int e) { return ot * 32 + 8 * (e / 4) + 4 * half + (e % 4); };
+      VN ad[2][GE], ax[2][GE];
+      auto fetch = [&](int g) {
+#pragma unroll
+        for (int k = 0; k < GE; ++k) {
+          const int o = row(g * GE + k);
+          const long long idx = ((long long)b * a.O + (o < a.O ? o : a.O - 1)) * V + v;
+          if constexpr (ADD) ad[g & 1][k] = *reinterpret_cast<const VN*>(a.add + idx);
+          if constexpr (AUX) ax[g & 1][k] = *reinterpret_cast<const VN*>(a.aux + idx);
+        }
+      };
+      fetch(0);
       f32x16 acc[NT];
 #pragma unroll
       for (int k = 0; k < NT; ++k) acc[k] = f32x16{0};
@@ -130,7 +153,11 @@ __global__ __launch_bounds__(256) void k_pointwise(PwArgs a) {
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int o = ot * 32 + 8 * (e / 4) + 4 * half + (e % 4);
+        if (e % GE == 0 && e / GE + 1 < NG) {
+          fetch(e / GE + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const int o = row(e);
         if (o >= a.O) continue;
         const long long idx = ((long long)b * a.O + o) * V + v;
         float val[NT];
@@ -141,17 +168,13 @@ __global__ __launch_bounds__(256) void k_pointwise(PwArgs a) {
 #pragma unroll
           for (int k = 0; k < NT; ++k) val[k] += bo;
         }
-        if (a.add) {
-          float ad[NT];
-          vload<NT>(a.add + idx, ad);
+        if constexpr (ADD) {
 #pragma unroll
-          for (int k = 0; k < NT; ++k) val[k] += ad[k];
+          for (int k = 0; k < NT; ++k) val[k] += ad[(e / GE) & 1][e % GE][k];
         }
-        if (a.aux) {
-          float ax[NT];
-          vload<NT>(a.aux + idx, ax);
+        if constexpr (AUX) {
 #pragma unroll
-          for (int k = 0; k < NT; ++k) val[k] *= gelu_grad(ax[k]);
+          for (int k = 0; k < NT; ++k) val[k] *= gelu_grad(ax[(e / GE) & 1][e % GE][k]);
         }
         if (a.out) vstore<NT>(a.out + idx, val);
         if (a.out_act) {
@@ -165,28 +188,35 @@ __global__ __launch_bounds__(256) void k_pointwise(PwArgs a) {
   }
 }
 
+template <int KS, int NT> hipError_t pointwise(const PwArgs& a, dim3 g, hipStream_t s) {
+  if (a.add && a.aux) hipLaunchKernelGGL((k_pointwise<KS, NT, true, true>), g, 256, 0, s, a);
+  else if (a.add) hipLaunchKernelGGL((k_pointwise<KS, NT, true, false>), g, 256, 0, s, a);
+  else if (a.aux) hipLaunchKernelGGL((k_pointwise<KS, NT, false, true>), g, 256, 0, s, a);
+  else hipLaunchKernelGGL((k_pointwise<KS, NT, false, false>), g, 256, 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_pointwise(const PwArgs& a, hipStream_t s) {
   if (a.ipad % 16 || a.opad % 32 || a.ipad > 16 * kMaxKs || a.V % 128) return hipErrorInvalidValue;
   const int ks = a.ipad / 16;
-  const int nt = ks <= 2 ? 4 : (ks <= 8 ? 2 : 1);
+  const int nt = ks <= 1 ? 4 : (ks <= 8 ? 2 : 1);
   const long long nblk = (long long)a.B * (a.V / (32 * nt));
   long long blocks = (nblk + 3) / 4;
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
   const dim3 g((unsigned)blocks);
   switch (ks) {
-    case 1: hipLaunchKernelGGL((k_pointwise<1, 4>), g, 256, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_pointwise<2, 4>), g, 256, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_pointwise<4, 2>), g, 256, 0, s, a); break;
-    case 6: hipLaunchKernelGGL((k_pointwise<6, 2>), g, 256, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_pointwise<8, 2>), g, 256, 0, s, a); break;
-    case 10: hipLaunchKernelGGL((k_pointwise<10, 1>), g, 256, 0, s, a); break;
-    case 12: hipLaunchKernelGGL((k_pointwise<12, 1>), g, 256, 0, s, a); break;
-    case 14: hipLaunchKernelGGL((k_pointwise<14, 1>), g, 256, 0, s, a); break;
-    case 16: hipLaunchKernelGGL((k_pointwise<16, 1>), g, 256, 0, s, a); break;
+    case 1: return pointwise<1, 4>(a, g, s);
+    case 2: return pointwise<2, 2>(a, g, s);
+    case 4: return pointwise<4, 2>(a, g, s);
+    case 6: return pointwise<6, 2>(a, g, s);
+    case 8: return pointwise<8, 2>(a, g, s);
+    case 10: return pointwise<10, 1>(a, g, s);
+    case 12: return pointwise<12, 1>(a, g, s);
+    case 14: return pointwise<14, 1>(a, g, s);
+    case 16: return pointwise<16, 1>(a, g, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

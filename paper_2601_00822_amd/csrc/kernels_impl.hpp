@@ -2143,7 +2143,7 @@ __global__ __launch_bounds__((GSched<T, NG, V>::NTH)) __attribute__((amdgpu_wave
     if constexpr (MODE == M_KCONV) {
       // the solves' shares of one tile run together, so that the tile of the
       // kernel spectrum (s d components, six times a force's) comes from the L2
-      // of their XCD after the first: 277 us for 32 forces on 64^3 in FP64 where
+      // of their XCD after the first: 268 us for 32 forces on 64^3 in FP64 where
       // solve after solve took 353
       const int per = descs[items[0].inst].items_g, ni = n_items / per;
       if (per * ni == n_items) e = (w % ni) * per + w / ni;
