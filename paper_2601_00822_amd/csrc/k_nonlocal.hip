@@ -12,6 +12,7 @@
 // registers.  A read of the LDS per offset and voxel bounded the kernels
 // before: 523 of them per voxel at delta = 5.  Columns cost 69 (ZV + 8) / ZV
 // there, 207 at ZV = 4 and 138 at ZV = 8.
+#include <atomic>
 #include <hip/hip_runtime.h>
 
 #include <vector>
@@ -553,30 +554,69 @@ Geom pick(int dim, const int n[3], int R, int zv) {
   return 4LL * G.ntA * G.ntB * G.ntC <= 5LL * H.ntA * H.ntB * H.ntC ? G : H;
 }
 
+// Fixed device scratch for a call's tables and work area: allocating and freeing the
+// matrix form's 2 MB took 45 us of the 517 of its two calls at 64^3 (472 now; the
+// scalar form's 0.2 MB cost nothing measurable, 576 and 575).
+// A device's copy belongs to one call at a time, which holds it until its stream has
+// drained; a second call meanwhile, or one that needs more, allocates.
+constexpr size_t kScratch = 4u << 20;
+__device__ __align__(256) char nl_scratch[kScratch];
+constexpr int kMaxDevices = 64;
+std::atomic<bool> scratch_held[kMaxDevices];
+
+struct Scratch {
+  int device = -1;   // held
+  char* claim(size_t bytes) {
+    int d = -1;
+    void* p = nullptr;
+    if (bytes > kScratch || hipGetDevice(&d) != hipSuccess || d < 0 || d >= kMaxDevices) return nullptr;
+    if (scratch_held[d].exchange(true, std::memory_order_acquire)) return nullptr;
+    device = d;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(nl_scratch)) != hipSuccess) p = nullptr;
+    if (!p) release();
+    return static_cast<char*>(p);
+  }
+  void release() {
+    if (device >= 0) scratch_held[device].store(false, std::memory_order_release);
+    device = -1;
+  }
+};
+
 // device copy of a call's tables (ints first, then doubles) followed by the
-// work area; freed with it
+// work area; given back with it
 struct Tables {
-  char* buf = nullptr;
+  char* buf = nullptr;      // allocated
+  Scratch scratch;          // or held
+  hipStream_t stream = nullptr;
   const int* ints = nullptr;
   const double* vals = nullptr;
   double* work = nullptr;
   ~Tables() {
     if (buf) (void)hipFree(buf);
+    if (scratch.device >= 0) {
+      (void)hipStreamSynchronize(stream);   // also after an error: nothing queued may use it any more
+      scratch.release();
+    }
   }
   hipError_t upload(const std::vector<int>& i, const std::vector<double>& v, size_t nwork, hipStream_t st) {
     const size_t b_i = (sizeof(int) * i.size() + 255) / 256 * 256, b_v = (sizeof(double) * v.size() + 255) / 256 * 256;
     host.resize(b_i + sizeof(double) * v.size());
     std::copy(i.begin(), i.end(), reinterpret_cast<int*>(host.data()));
     std::copy(v.begin(), v.end(), reinterpret_cast<double*>(host.data() + b_i));
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&buf), b_i + b_v + sizeof(double) * nwork + 256);
-    if (e != hipSuccess) {
-      buf = nullptr;
-      return hipErrorOutOfMemory;
+    const size_t bytes = b_i + b_v + sizeof(double) * nwork + 256;
+    stream = st;
+    char* at = scratch.claim(bytes);
+    if (!at) {
+      if (hipMalloc(reinterpret_cast<void**>(&buf), bytes) != hipSuccess) {
+        buf = nullptr;
+        return hipErrorOutOfMemory;
+      }
+      at = buf;
     }
-    ints = reinterpret_cast<const int*>(buf);
-    vals = reinterpret_cast<const double*>(buf + b_i);
-    work = reinterpret_cast<double*>(buf + b_i + b_v);
-    return hipMemcpyAsync(buf, host.data(), host.size(), hipMemcpyHostToDevice, st);
+    ints = reinterpret_cast<const int*>(at);
+    vals = reinterpret_cast<const double*>(at + b_i);
+    work = reinterpret_cast<double*>(at + b_i + b_v);
+    return hipMemcpyAsync(at, host.data(), host.size(), hipMemcpyHostToDevice, st);
   }
   std::vector<char> host;   // outlives the copy: every caller synchronises before this goes
 };

@@ -53,3 +53,43 @@ def test_tile_edges(shape, delta, deg, form, ns):
     for k in range(ns):
         want = N.apply_operator(c, us[k], delta, form)
         np.testing.assert_allclose(out[k], want, rtol=0, atol=1e-12 * np.abs(want).max(), err_msg=f"sample {k}")
+
+
+def test_threads_share_no_scratch():
+    """Calls that overlap in time, from threads with streams of their own, give the
+    bits that they give one after another."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import threading
+    from paper_2601_00822_amd import nonlocal_apply, nonlocal_normal_equations
+    say("nonlocal calls from three threads")
+    jobs = []
+    for k, (shape, delta, deg, form) in enumerate([((16, 16, 32), 3.0, 4, 0), ((8, 16, 16), 2.5, 6, 1), ((64, 65), 4.0, 3, 1)]):
+        rng = np.random.default_rng(k)
+        d = len(shape)
+        U, Gm = (torch.from_numpy(rng.normal(size=(2, d) + shape)).cuda() for _ in range(2))
+        jobs.append((U, Gm, deg, delta, form, rng.normal(size=(form + 1) * (deg + 1))))
+
+    def run(job):
+        U, Gm, deg, delta, form, c = job
+        G, g, gg = nonlocal_normal_equations(U, Gm, deg, delta, form)
+        return np.array(G), np.array(g), gg, nonlocal_apply(U, c, delta, form).cpu().numpy()
+
+    alone = [run(j) for j in jobs]
+    torch.cuda.synchronize()
+    bad = []
+
+    def worker(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(10):
+                got = run(jobs[k])
+                if not all(np.array_equal(a, b) for a, b in zip(got, alone[k])):
+                    bad.append(k)
+
+    threads = [threading.Thread(target=worker, args=(k,)) for k in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
