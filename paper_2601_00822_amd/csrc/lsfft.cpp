@@ -107,7 +107,8 @@ struct BatchGroup {
 enum ListId { L_XLEAD, L_YLEAD, L_GLEAD, L_X, L_Y, L_P, L_G, L_CG, L_XALL, L_YALL, L_GALL, L_NUM };
 
 // A contiguous run of work items of one list that share the kernel
-// specialization (dimension and transform length) and therefore one launch.
+// specialization (dimension, transform length, schedule variant) and therefore
+// one launch.
 struct Seg {
   int dim = 0, len = 0;
   int var = 0;         // schedule variant of the pass kernel
@@ -152,8 +153,12 @@ struct lsfft_plan_s {
   int64_t kt_n[LSFFT_K_COUNT] = {0};
   bool timing_active = false;
   // schedule variant per pass kind (0 x, 1 y, 2 outer) and length index,
-  // used by FP32 3D solves (lsfft_autotune, lsfft_schedule_set, the cache)
-  int sched[3][kNumLens] = {};
+  // used by FP32 3D solves (lsfft_autotune, lsfft_schedule_set, the cache);
+  // -1: not chosen, the default
+  int sched[3][kNumLens];
+  lsfft_plan_s() {
+    for (auto& kind : sched) std::fill(kind, kind + kNumLens, -1);
+  }
   // spectral layout per grid (index into grids): 1 kx-blocked between the y
   // and outer passes where the grid allows it, 0 rows throughout
   std::vector<int> layout;
@@ -264,6 +269,12 @@ bool geometry(bool f64, const lsfft_grid& g, const int sched[3][kNumLens], Geome
   const int outer = (g.dim == 3) ? o->nz : o->ny;
   o->var_x = plan_variant(sched, f64, g.dim, 0, o->nx);
   o->var_y = (g.dim == 3) ? plan_variant(sched, f64, g.dim, 1, o->ny) : 0;
+  // Nobody chose: tiles of 16 pencils of 256 points instead of 8 where there are
+  // enough of them to fill the chip, 950 against 1021 us per iteration at 256^3
+  // (the y passes 343 of 402), 256 against 275 at 128 x 256 x 128; with 16 planes
+  // of 256 x 128 66 against 61, and no difference for 64 of 256 x 64.  The same
+  // plan of radices, so the same bits.
+  if (g.dim == 3 && !f64 && o->ny == 256 && sched[1][len_index(256)] < 0 && (long long)o->nz * o->H >= 4096) o->var_y = 1;
   o->var_g = plan_variant(sched, f64, g.dim, 2, outer);
   o->lds_x = query_geometry(f64, 0, o->nx, o->var_x, &mr);
   o->lds_xi = query_geometry(f64, 3, o->nx, o->var_x, nullptr);
@@ -486,7 +497,7 @@ lsfft_status upload_lists(Batch& b, const std::vector<int>& running, bool all_to
         if (items == 0) continue;
         Seg* sg = nullptr;
         for (auto& x : b.segs[l])
-          if (x.dim == dim && x.len == len) sg = &x;
+          if (x.dim == dim && x.len == len && x.var == var) sg = &x;
         if (!sg) {
           b.segs[l].push_back(Seg{});
           sg = &b.segs[l].back();
@@ -532,7 +543,7 @@ lsfft_status upload_lists(Batch& b, const std::vector<int>& running, bool all_to
         int dim, len, cnt, var;
         size_t lds;
         list_key(b, l, i, &dim, &len, &cnt, &lds, &var);
-        if (cnt == 0 || dim != x.dim || len != x.len) continue;
+        if (cnt == 0 || dim != x.dim || len != x.len || var != x.var) continue;
         for (int k = 0; k < cnt; ++k) items[x.off + fill + k] = WorkItem{i, k};
         fill += cnt;
       }

@@ -111,3 +111,28 @@ def test_schemes(dev, scheme):
     plan.close()
     assert rep.status == 0
     assert O.relative_strain_error_voigt(out["eps"].double().cpu().numpy(), O.to_voigt(ref.eps)) <= 1e-5
+
+
+@pytest.mark.parametrize("shapes", [[(32, 256, 256)], [(32, 256, 256), (4, 256, 16)]])
+def test_default_y_tiles_of_256(dev, shapes):
+    # the default of large grids and the one chosen by hand, also in a batch with a
+    # small grid of the same length, which keeps the other tiles: the same bits
+    import torch
+    from paper_2601_00822_amd import Plan
+    probs = []
+    for g, shp in enumerate(shapes):
+        phase, f = problem(shp, 3 + g)
+        probs.append(dict(grid=g, phase=torch.from_numpy(phase).to(dev), lame=LAME3, f=torch.from_numpy(f).to(dev)))
+    outs = []
+    for variant in (None, 0, 1):
+        say(f"{shapes} y variant {variant}")
+        plan = Plan(shapes, prec="f32", scheme="basic", max_batch=len(shapes))
+        if variant is not None:
+            plan.set_schedule("y", 256, variant)
+        out, reps, _ = plan.solve_batch(probs, tol=1e-12, max_iter=3)
+        torch.cuda.synchronize()
+        outs.append([o["eps"].clone() for o in out])
+        plan.close()
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert torch.equal(a, b)
