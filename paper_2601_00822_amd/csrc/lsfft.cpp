@@ -1918,7 +1918,11 @@ lsfft_status lsfft_iteration_bytes(lsfft_plan_t p, int grid_idx, int kernel_clas
   double b = 0.0;
   switch (kernel_class) {
     case LSFFT_K_XPASS: b = 2 * s * comp + (double)g.nvox; break;          // eps^ in, sigma^ out, phase
-    case LSFFT_K_YPASS: b = (g.dim == 3) ? 4 * s * comp : 0.0; break;       // two sweeps, in and out
+    case LSFFT_K_YPASS:
+      // two sweeps, in and out; none where k_plane does them in the x pass's place
+      // (timed plans keep the passes)
+      b = (g.dim == 3 && !(g.lds_p && !(p->flags & LSFFT_TIMING))) ? 4 * s * comp : 0.0;
+      break;
     case LSFFT_K_GREEN:
       if (p->scheme == LSFFT_ANDERSON) {
         // residual pass: sigma^, f^, x_k, x_{k-1}, F_{k-1}, m - 1 older dF in;
