@@ -381,6 +381,7 @@ struct Batch {
   double tol = 1e-8;
   int max_iter = 0;
   bool averaging = false;
+  bool sums32 = false;   // FP64 companion of solves whose FP32 fields are averaged
   // the captured polling round, kept for the batch's lifetime (the inner
   // solves of the defect correction replay it once per outer step)
   struct GraphHolder {
@@ -912,6 +913,8 @@ lsfft_status read_states(Batch& b, std::vector<int>& running) {
 // faster than one CU, see k_solve2d.hip), else 0.
 size_t fits_solve2d(const Batch& b) {
   if (b.p->scheme != LSFFT_BASIC) return 0;
+  // FP64 sums of FP32 fields keep their digits: there the launches' roundings stay
+  if (b.sums32 || (!b.p->f64 && b.averaging)) return 0;
   size_t lds = 0;
   for (size_t i = 0; i < b.specs.size(); ++i) {
     const Geometry& g = b.geo[i];
@@ -1184,6 +1187,7 @@ lsfft_status run_refined(Batch& b, lsfft_report* rep, double t0_wall) {
   c.tol = b.tol;
   c.max_iter = kMaxOuter;
   c.averaging = false;
+  c.sums32 = b.averaging;
   c.specs = b.specs;
   for (int i = 0; i < n; ++i) {
     Spec& s = c.specs[i];
