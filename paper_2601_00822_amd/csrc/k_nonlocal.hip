@@ -133,10 +133,11 @@ __device__ __forceinline__ void stage(const Geom& G, const T* __restrict__ u, co
 // ---------------------------------------------------------------------------
 // Offsets folded into classes: the columns (dA, dB) of one |dA|, |dB| pair (in
 // either order in 3D) share every weight, so their sum E along C is formed
-// first, then E(c + dC) + E(c - dC).  cls[4 k]: columns of class k
+// first, then E(c + dC) + E(c - dC), less u(x) as often as there are offsets in
+// it: subtracted once for the whole horizon instead, the error of a field with a
+// rigid offset was 2 to 24 times larger (horizons 1.5 to 6).  cls[4 k]: columns of class k
 // (first, count), its largest dC, and its first weight row; `col` holds the
-// columns' LDS offsets.  The weight of r = 0 is minus the sum of all others
-// (the -u(x) terms).
+// columns' LDS offsets.  Class 0 is the column of r = 0, which itself is left out.
 template <typename T, int R, int DIM, int ZV>
 __device__ __forceinline__ void column_sums(const T* lds, int base, const int* __restrict__ col, int n,
                                             double (&E)[ZV + 2 * R]) {
@@ -167,7 +168,7 @@ __device__ __forceinline__ void column_sums(const T* lds, int base, const int* _
 // Gamma . Gamma per thread in FP64; the workgroup's sums go to its slot.
 // Bound by FP64 issue (about 620 operations per voxel and component at
 // delta = 5, degree 6) and LDS reads (207).  On eight 64^3 FP64 fields there:
-// 322 us, against 1250 us with a read per offset and a triangle of nine
+// 327 us, against 1250 us with a read per offset and a triangle of nine
 // features whatever the degree.
 template <typename T, int R, int DIM, int NF>
 __global__ __launch_bounds__(NT) void k_nl_gram(Geom G, const T* __restrict__ u, const T* __restrict__ gam, int nsample,
@@ -193,11 +194,13 @@ __global__ __launch_bounds__(NT) void k_nl_gram(Geom G, const T* __restrict__ u,
       __syncthreads();
       stage<1>(G, u + comp, s, tab, lds);
       __syncthreads();
-      double phi[ZV][NF];
+      double phi[ZV][NF], u0[ZV];
 #pragma unroll
-      for (int v = 0; v < ZV; ++v)
+      for (int v = 0; v < ZV; ++v) {
+        u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
 #pragma unroll
         for (int m = 0; m < NF; ++m) phi[v][m] = 0.0;
+      }
       for (int q = 0; q < ncls; ++q) {
         const int c0 = cls[4 * q], cn = cls[4 * q + 1], zr = cls[4 * q + 2];
         const double* w = W + cls[4 * q + 3] * NF;
@@ -206,9 +209,11 @@ __global__ __launch_bounds__(NT) void k_nl_gram(Geom G, const T* __restrict__ u,
 #pragma unroll
         for (int d = 0; d <= R; ++d) {
           if (d > zr) break;
+          if (d == 0 && q == 0) continue;
+          const double n = double(d ? 2 * cn : cn);
 #pragma unroll
           for (int v = 0; v < ZV; ++v) {
-            const double D = d ? E[v + R + d] + E[v + R - d] : E[v + R];
+            const double D = __builtin_fma(-n, u0[v], d ? E[v + R + d] + E[v + R - d] : E[v + R]);
 #pragma unroll
             for (int m = 0; m < NF; ++m) phi[v][m] += w[d * NF + m] * D;
           }
@@ -249,7 +254,7 @@ __global__ __launch_bounds__(NT) void k_nl_gram(Geom G, const T* __restrict__ u,
 
 // The fitted scalar operator, one workgroup per (sample, tile): LDS reads
 // (138 per voxel and component at delta = 5) bound it.  On eight 64^3 FP64
-// fields there: 227 us, against 601 us with a read per offset.
+// fields there: 235 us, against 601 us with a read per offset.
 template <typename T, int R, int DIM>
 __global__ __launch_bounds__(NT) void k_nl_apply(Geom G, const T* __restrict__ u, int nsample,
                                                  const int* __restrict__ cls, int ncls, const int* __restrict__ col,
@@ -270,9 +275,12 @@ __global__ __launch_bounds__(NT) void k_nl_apply(Geom G, const T* __restrict__ u
     __syncthreads();
     stage<1>(G, u + comp, s, tab, lds);
     __syncthreads();
-    double r[ZV];
+    double r[ZV], u0[ZV];
 #pragma unroll
-    for (int v = 0; v < ZV; ++v) r[v] = 0.0;
+    for (int v = 0; v < ZV; ++v) {
+      r[v] = 0.0;
+      u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
+    }
     for (int q = 0; q < ncls; ++q) {
       const int c0 = cls[4 * q], cn = cls[4 * q + 1], zr = cls[4 * q + 2];
       const double* w = kw + cls[4 * q + 3];
@@ -281,8 +289,11 @@ __global__ __launch_bounds__(NT) void k_nl_apply(Geom G, const T* __restrict__ u
 #pragma unroll
       for (int d = 0; d <= R; ++d) {
         if (d > zr) break;
+        if (d == 0 && q == 0) continue;
+        const double n = double(d ? 2 * cn : cn);
 #pragma unroll
-        for (int v = 0; v < ZV; ++v) r[v] += w[d] * (d ? E[v + R + d] + E[v + R - d] : E[v + R]);
+        for (int v = 0; v < ZV; ++v)
+          r[v] += w[d] * __builtin_fma(-n, u0[v], d ? E[v + R + d] + E[v + R - d] : E[v + R]);
       }
     }
 #pragma unroll
@@ -294,14 +305,18 @@ __global__ __launch_bounds__(NT) void k_nl_apply(Geom G, const T* __restrict__ u
 // ---------------------------------------------------------------------------
 // matrix form
 // ---------------------------------------------------------------------------
-// The fitted matrix operator: per staged input component b and column
-// (dA, dB), out_a += sum over dC of (K1 delta_ab + K2 e_a e_b) u_b(x + r).
-// cls[4 k] holds one column each here (its LDS offset, 1, largest dC, row of
-// dC = 0); kw has the three coefficients [a] per offset, one table per b.  The
-// coefficients of r = 0 are minus the sum of the others.
-// FP64 issue bounds it (276 multiply-adds per voxel and input component at
+// The fitted matrix operator: per staged input component b and pair of offsets
+// r, -r, whose coefficients are the same,
+//   out_a += (K1 delta_ab + K2 e_a e_b) ((u_b(x + r) - u_b(x)) + (u_b(x - r) - u_b(x))).
+// The differences are formed first, so that a constant field gives zero and a
+// rigid offset costs no digits (weights times u(x + r), less their sum times u(x),
+// lost 4e5 in accuracy at an offset of 1e6).  cls[4 k] holds a column (dA, dB) and
+// its opposite (their LDS offsets), the largest dC and the row of dC = 0; the
+// column of r = 0 is its own opposite and takes dC > 0 only.  kw has the three
+// coefficients [a] per offset of the first column, one table per b.
+// FP64 issue bounds it (276 operations per voxel and input component at
 // delta = 3, on 21 (ZV + 4) / ZV LDS reads).  On eight 64^3 FP64 fields there:
-// 127 us, against 298 us with a read per offset.
+// 107 us, against 298 us with a read per offset.
 template <typename T, int R, int DIM>
 __global__ __launch_bounds__(NT) void k_nl_apply1(Geom G, const T* __restrict__ u, int nsample,
                                                   const int* __restrict__ cls, int ncls,
@@ -327,21 +342,29 @@ __global__ __launch_bounds__(NT) void k_nl_apply1(Geom G, const T* __restrict__ 
     __syncthreads();
     stage<1>(G, u + ((long long)k * DIM + b) * nvox, s, tab, lds);
     __syncthreads();
-    for (int q = 0; q < ncls; ++q) {
-      const int zr = cls[4 * q + 2];
-      const T* p = lds + s.base + cls[4 * q];
-      double E[ZV + 2 * R];
+    double u0[ZV];
 #pragma unroll
-      for (int w = 0; w < ZV + 2 * R; ++w) E[w] = double(p[w * Pitch<R, DIM>::C]);
+    for (int v = 0; v < ZV; ++v) u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
+    for (int q = 0; q < ncls; ++q) {
+      const int o1 = cls[4 * q], o2 = cls[4 * q + 1], zr = cls[4 * q + 2];
+      const T* p1 = lds + s.base + o1;
+      const T* p2 = lds + s.base + o2;
+      double E1[ZV + 2 * R], E2[ZV + 2 * R];
+#pragma unroll
+      for (int w = 0; w < ZV + 2 * R; ++w) {
+        E1[w] = double(p1[w * Pitch<R, DIM>::C]);
+        E2[w] = double(p2[w * Pitch<R, DIM>::C]);
+      }
       const double* cf = kw + (long long)b * nkw + 3 * cls[4 * q + 3];   // the row of dC = 0
+      const int lo = o1 == o2 ? 1 : -zr;
 #pragma unroll
       for (int d = -R; d <= R; ++d) {
-        if (d < -zr || d > zr) continue;
+        if (d < lo || d > zr) continue;
         const double* e = cf + 3 * d;
         const double e0 = e[0], e1 = e[1], e2 = e[2];
 #pragma unroll
         for (int v = 0; v < ZV; ++v) {
-          const double x = E[v + R + d];
+          const double x = (E1[v + R + d] - u0[v]) + (E2[v + R - d] - u0[v]);
           r[0][v] += e0 * x;
           r[1][v] += e1 * x;
           r[2][v] += e2 * x;
@@ -628,14 +651,12 @@ hipError_t allow_lds(K kernel, size_t bytes) {
                              (int)bytes);
 }
 
-// classes of the scalar form: fn(|r|^2) -> weight row of nw doubles; the row
-// of r = 0 is minus the sum of all the others over the horizon
+// classes of the scalar form: row(|r|^2) -> weight row of nw doubles; the row of
+// r = 0 is not used
 template <typename Fn>
 void scalar_classes(const Geom& G, int R, double delta, int nw, Fn&& row, std::vector<int>& ints,
                     std::vector<double>& vals, int& ncls) {
   std::vector<int> cls, col;
-  std::vector<double> total(nw, 0.0);
-  size_t zero_at = 0;
   const bool three = G.dim == 3;
   auto inside = [&](int rr) { return std::sqrt((double)rr) < delta; };
   for (int p = 0; p <= R; ++p)
@@ -654,18 +675,11 @@ void scalar_classes(const Geom& G, int R, double delta, int nw, Fn&& row, std::v
       const int n = (int)col.size() - c0;
       cls.insert(cls.end(), {c0, n, zr, (int)(vals.size() / nw)});
       for (int d = 0; d <= zr; ++d) {
-        if (p == 0 && q == 0 && d == 0) {
-          zero_at = vals.size();
-          vals.resize(vals.size() + nw, 0.0);
-          continue;
-        }
         const size_t at = vals.size();
         vals.resize(at + nw, 0.0);
-        row(p * p + q * q + d * d, &vals[at]);
-        for (int m = 0; m < nw; ++m) total[m] += vals[at + m] * n * (d ? 2 : 1);
+        if (p || q || d) row(p * p + q * q + d * d, &vals[at]);
       }
     }
-  for (int m = 0; m < nw; ++m) vals[zero_at + m] = -total[m];
   ncls = (int)cls.size() / 4;
   ints = cls;
   ints.insert(ints.end(), col.begin(), col.end());
@@ -856,34 +870,25 @@ hipError_t apply_form(int dim, const int n[3], int R, double delta, int form, in
     scalar_classes(G, R, delta, 1, [&](int rr, double* w) { *w = kernel_at(rr, 0); }, ints, vals, ncls);
   } else {
     std::vector<double> tab[3];
-    double total[9] = {0};
-    size_t zero_at = 0;
     const int rb = dim == 3 ? R : 0;
     auto inside = [&](int rr) { return std::sqrt((double)rr) < delta; };
-    for (int db = -rb; db <= rb; ++db)
-      for (int da = -R; da <= R; ++da) {
+    for (int db = 0; db <= rb; ++db)
+      for (int da = db ? -R : 0; da <= R; ++da) {   // one column of each pair of opposites
         if (!inside(da * da + db * db)) continue;
         int zr = 0;
         while (zr < R && inside(da * da + db * db + (zr + 1) * (zr + 1))) ++zr;
-        ints.insert(ints.end(), {db * G.la + da, 1, zr, (int)(tab[0].size() / 3) + zr});
+        const int at = db * G.la + da;
+        ints.insert(ints.end(), {at, -at, zr, (int)(tab[0].size() / 3) + zr});
         for (int dc = -zr; dc <= zr; ++dc) {
           const int rr = da * da + db * db + dc * dc;
           const double rho = rr ? std::sqrt((double)rr) : 1.0;
           const double k1 = rr ? kernel_at(rr, 0) : 0.0, k2 = rr ? kernel_at(rr, 1) : 0.0;
           const double e[3] = {da / rho, (dim == 3 ? db : dc) / rho, (dim == 3 ? dc : 0) / rho};
-          if (rr == 0) zero_at = tab[0].size();
           for (int b = 0; b < 3; ++b)
-            for (int a = 0; a < 3; ++a) {
-              const double v = k2 * e[a] * e[b] + (a == b ? k1 : 0.0);
-              tab[b].push_back(v);
-              total[3 * b + a] += v;
-            }
+            for (int a = 0; a < 3; ++a) tab[b].push_back(k2 * e[a] * e[b] + (a == b ? k1 : 0.0));
         }
       }
-    for (int b = 0; b < 3; ++b) {
-      for (int a = 0; a < 3; ++a) tab[b][zero_at + a] = -total[3 * b + a];
-      vals.insert(vals.end(), tab[b].begin(), tab[b].end());
-    }
+    for (int b = 0; b < 3; ++b) vals.insert(vals.end(), tab[b].begin(), tab[b].end());
     ncls = (int)ints.size() / 4;
   }
   Tables t;

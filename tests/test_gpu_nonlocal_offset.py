@@ -1,0 +1,116 @@
+"""The nonlocal operator on fields with a rigid offset, which it does not see: the
+accuracy on them is that of forming differences first.
+
+The inputs are white noise of unit variance plus a constant per component, the
+reference the same grid values in extended precision.
+  matrix form  every u(x + r) - u(x) is exact here up to one rounding, so the error
+               is that of the fluctuation alone: the bar of the parity tests, 1e-12
+               of the largest value.  A constant field gives zero.
+  scalar form  sums of raw values, less u(x) as often: at least as accurate (root
+               mean square) as sums by shell of equal |r|, the order evaluated here.
+  normal equations  features of the same sums: rounding of the values' size, eps
+               times the offset per term, over fluctuations of unit size; at 1e4
+               1e-10 of the largest entry leaves a margin of 20.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import nonlocal_oracle as N
+
+pytestmark = pytest.mark.gpu
+
+CASES = [((8, 12, 33), 3.0, 6), ((12, 9, 17), 2.5, 3), ((9, 16, 16), 5.0, 6), ((40, 33), 3.0, 4), ((14, 13, 20), 6.5, 8)]
+OFFSET = (1.0e6, -3.0e5, 2.0e6)
+
+
+def say(msg):
+    print(f"\n[case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+def torch_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def field(shape, seed, scale):
+    d = len(shape)
+    u = np.random.default_rng(seed).normal(size=(d,) + shape)
+    for a in range(d):
+        u[a] += scale * OFFSET[a]
+    return u
+
+
+def terms(u, c, delta, form):
+    """(extended precision result, scalar form by shells in FP64)"""
+    d = u.ndim - 1
+    offs, rho = N.ball_offsets(d, delta)
+    M = len(c) // (form + 1) - 1
+    w = N.bernstein(M, rho / delta)
+    k1 = c[:M + 1] @ w
+    k2 = c[M + 1:] @ w if form else None
+    axes = tuple(range(1, d + 1))
+    ul = u.astype(np.longdouble)
+    exact = np.zeros_like(ul)
+    shells = {}
+    for i, r in enumerate(offs):
+        raw = np.roll(u, shift=tuple(-int(v) for v in r), axis=axes)
+        diff = raw.astype(np.longdouble) - ul
+        exact += np.longdouble(k1[i]) * diff
+        if form:
+            e = r[::-1].astype(np.longdouble) / np.sqrt(np.longdouble((r * r).sum()))
+            exact += np.longdouble(k2[i]) * e.reshape((d,) + (1,) * d) * np.tensordot(e, diff, axes=(0, 0))
+        q = int((r * r).sum())
+        s, n, _ = shells.get(q, (0.0, 0, 0.0))
+        shells[q] = (s + raw, n + 1, k1[i])
+    byshell = np.zeros_like(u)
+    for q in sorted(shells):
+        s, n, k = shells[q]
+        byshell += k * (s - n * u)
+    return exact, byshell
+
+
+@pytest.mark.parametrize("shape,delta,deg", CASES)
+def test_matrix_operator(shape, delta, deg):
+    torch = torch_gpu()
+    from paper_2601_00822_amd import nonlocal_apply
+    say(f"matrix operator {shape} delta {delta} degree {deg}")
+    c = np.random.default_rng(deg).normal(size=2 * (deg + 1))
+    u = field(shape, 3, 1.0)
+    got = nonlocal_apply(torch.from_numpy(u[None]).cuda(), c, delta, 1).cpu().numpy()[0]
+    want, _ = terms(u, c, delta, 1)
+    np.testing.assert_allclose(got, want.astype(np.float64), rtol=0, atol=1e-12 * float(np.abs(want).max()))
+    flat = np.full((1, len(shape)) + shape, 0.1)
+    assert not nonlocal_apply(torch.from_numpy(flat).cuda(), c, delta, 1).any()
+
+
+@pytest.mark.parametrize("shape,delta,deg", CASES)
+def test_scalar_operator(shape, delta, deg):
+    torch = torch_gpu()
+    from paper_2601_00822_amd import nonlocal_apply
+    say(f"scalar operator {shape} delta {delta} degree {deg}")
+    c = np.random.default_rng(deg).normal(size=deg + 1)
+    u = field(shape, 4, 1.0)
+    got = nonlocal_apply(torch.from_numpy(u[None]).cuda(), c, delta, 0).cpu().numpy()[0]
+    exact, byshell = terms(u, c, delta, 0)
+    rms = lambda v: float(np.sqrt(np.mean(((v - exact) ** 2).astype(np.float64))))
+    print(f"error {rms(got):.2e}, by shells {rms(byshell):.2e}")
+    assert rms(got) <= rms(byshell)
+
+
+@pytest.mark.parametrize("form", [0, 1])
+def test_normal_equations(form):
+    torch = torch_gpu()
+    from paper_2601_00822_amd import nonlocal_normal_equations
+    shape, delta, deg = (9, 12, 33), 3.0, 4
+    say(f"normal equations {shape} form {form}")
+    u, gam = field(shape, 5, 1e-2), np.random.default_rng(6).normal(size=(3,) + shape)
+    U, Gm = (torch.from_numpy(v[None]).cuda() for v in (u, gam))
+    G, g, _ = nonlocal_normal_equations(U, Gm, deg, delta, form)
+    Gw, gw, ggw = N.normal_equations([u], [gam], deg, delta, form)
+    np.testing.assert_allclose(G, Gw, rtol=0, atol=1e-10 * np.abs(Gw).max())
+    np.testing.assert_allclose(g, gw, rtol=0, atol=1e-10 * np.abs(Gw).max() ** 0.5 * ggw ** 0.5)
