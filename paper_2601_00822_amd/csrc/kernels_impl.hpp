@@ -1645,9 +1645,12 @@ __device__ void green_item(const InstDesc& D, InstState* __restrict__ St, int lo
       pk0[q] = t.kx(m) == 0;
       pth[q] = t.other(m);
     }
-    if (t.kx0 != 0) {
-      // without the column: no branch between the points' loads, which are then in
-      // flight together (outside the grid the force is zero)
+    // Without the column: no branch between the points' loads, which are then in
+    // flight together (outside the grid the force is zero).  For 32 forces on 64^3
+    // in FP64 268 us against 277, 32 on 96^3 3827 against 3968 us per call; a
+    // second copy of the code costs more elsewhere: four forces on 128^3 1696
+    // against 1613 us per call, on 16^3 187 against 179.
+    if ((NG == 64 || NG == 96) && t.kx0 != 0) {
       inverse_all(SS, 0, std::integral_constant<int, S>{}, [&](int c, int q, int r, T& re, T& im) {
         re = T(0);
         im = T(0);
@@ -2140,13 +2143,18 @@ __global__ __launch_bounds__((GSched<T, NG, V>::NTH)) __attribute__((amdgpu_wave
   const int n_items = *nitems;
   for (int w = xcd_slot(blockIdx.x, gridDim.x); w < n_items; w += gridDim.x) {
     int e = w;
-    if constexpr (MODE == M_KCONV) {
+    if constexpr (MODE == M_KCONV && std::is_same<T, double>::value) {
       // the solves' shares of one tile run together, so that the tile of the
       // kernel spectrum (s d components, six times a force's) comes from the L2
       // of their XCD after the first: 268 us for 32 forces on 64^3 in FP64 where
-      // solve after solve took 353
-      const int per = descs[items[0].inst].items_g, ni = n_items / per;
-      if (per * ni == n_items) e = (w % ni) * per + w / ni;
+      // solve after solve took 353.  Not in FP32 (190 us for four forces on 128^3
+      // against 260, 167 for 32 on 64^3 against 202), nor where that L2 holds about
+      // the whole spectrum (288 us per call of 32 on 24^3 against 299; as many at
+      // 32^3, of 4.7 MB).
+      const InstDesc& D0 = descs[items[0].inst];
+      const int per = D0.items_g, ni = n_items / per;
+      const bool large = D0.Pc * (DIM * D0.ncomp_s * 2 * (int)sizeof(T)) > (8LL << 20);
+      if (large && per * ni == n_items) e = (w % ni) * per + w / ni;
     }
     const WorkItem it = items[e];
     const InstDesc& D = descs[it.inst];
