@@ -194,6 +194,12 @@ template <typename T, int NX, int NY> struct PlaneCfg {
   static_assert(W > 0, "a wave count for these lengths");
   static constexpr int NT = 64 * W, CW = H / W, RW = NY / W;
   static constexpr int EU = (NX % 3 == 0 || NY % 3 == 0) && W < 16 ? 3 : 4;   // waves per SIMD
+  // ... where there are more planes than CUs.  At three waves per SIMD a second
+  // workgroup of six waves does not get in beside the first: 48 x 96, six solves of
+  // 48 planes, 139 us per iteration (the three passes 123), with four waves 123, of 96
+  // planes 217 (204) and 190.  For one solve of 48 planes, 57 against 61 us (65), the
+  // registers of three waves.
+  static constexpr int EUB = W > 4 && W % 4 != 0 ? 4 : EU;
   static constexpr int p2(int n) { int p = 1; while (p < n) p *= 2; return p; }
   static constexpr int Q = p2(CW) < 16 ? p2(CW) : 16;
   static constexpr int HP = H + H / 8;
@@ -461,8 +467,8 @@ __device__ __forceinline__ void plane_item(const InstDesc& D, int local, const T
   }
 }
 
-template <typename T, int NX, int NY>
-__global__ __launch_bounds__((PlaneCfg<T, NX, NY>::NT)) __attribute__((amdgpu_waves_per_eu((PlaneCfg<T, NX, NY>::EU)))) void k_plane(
+template <typename T, int NX, int NY, int EU>
+__global__ __launch_bounds__((PlaneCfg<T, NX, NY>::NT)) __attribute__((amdgpu_waves_per_eu(EU))) void k_plane(
     const InstDesc* __restrict__ descs, InstState* states, const WorkItem* __restrict__ items,
     const int* __restrict__ nitems, const double* __restrict__ lame, const T* __restrict__ tw,
     const int* __restrict__ red_inst, const int* __restrict__ red_n) {
@@ -509,20 +515,26 @@ __global__ __launch_bounds__((PlaneCfg<T, NX, NY>::NT)) __attribute__((amdgpu_wa
 #define LSFFT_PLANES(X, T) \
   LSFFT_PLANE_Y(X, T, 32) LSFFT_PLANE_Y(X, T, 48) LSFFT_PLANE_Y(X, T, 64) LSFFT_PLANE_Y(X, T, 96) LSFFT_PLANE_Y(X, T, 128)
 
-template <typename T, int NX, int NY> hipError_t launch_one(const LaunchArgs& a) {
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane<T, NX, NY>),
+constexpr int kCus = 256;
+template <typename T, int NX, int NY, int EU> hipError_t launch_eu(const LaunchArgs& a) {
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane<T, NX, NY, EU>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
   if (e != hipSuccess) return e;
   // as many workgroups as fit the chip at once: the launch is captured for the
   // batch's first iteration, and of the later ones' fewer solves the surplus
   // workgroups would each wait for a CU only to find nothing to do
   using C = PlaneCfg<T, NX, NY>;
-  constexpr int kCus = 256, kPerCu = 4 * C::EU / C::W < (int)(160 * 1024 / (C::LDS + 1024)) ? 4 * C::EU / C::W : (int)(160 * 1024 / (C::LDS + 1024));
+  constexpr int kPerCu = 4 * EU / C::W < (int)(160 * 1024 / (C::LDS + 1024)) ? 4 * EU / C::W : (int)(160 * 1024 / (C::LDS + 1024));
   static_assert(kPerCu >= 1, "fits a CU");
   const dim3 grid(std::min<unsigned>(a.grid.x, kCus * kPerCu));
-  LSFFT_LAUNCH((k_plane<T, NX, NY>), grid, (PlaneCfg<T, NX, NY>::NT), a.lds, a.stream, a.desc, a.state, a.items,
+  LSFFT_LAUNCH((k_plane<T, NX, NY, EU>), grid, C::NT, a.lds, a.stream, a.desc, a.state, a.items,
                a.count, a.lame, static_cast<const T*>(a.tw), a.red_inst, a.red_n);
   return hipGetLastError();
+}
+template <typename T, int NX, int NY> hipError_t launch_one(const LaunchArgs& a) {
+  using C = PlaneCfg<T, NX, NY>;
+  if (C::EUB != C::EU && a.grid.x > kCus) return launch_eu<T, NX, NY, C::EUB>(a);
+  return launch_eu<T, NX, NY, C::EU>(a);
 }
 
 }  // namespace
