@@ -242,7 +242,7 @@ hipError_t backward(lsfft_fno_s* f, int B, const float* x, const float* t) {
   j.b1 = f->params + f->L.proj1.b_off;
   j.out = f->dbuf[cur];
   j.part1 = f->wpart;
-  j.part2 = f->wpart + (size_t)project_bwd_blocks(B, f->V) * (a.hidden * 33);
+  j.part2 = f->wpart + (size_t)project_bwd_blocks(B, f->V, a.hidden) * (a.hidden * 33);
   j.hidden = a.hidden;
   j.O = a.cout;
   j.opad16 = f->L.proj2.t_ipad;
@@ -314,7 +314,7 @@ lsfft_status lsfft_fno_create(lsfft_fno_t* out, const lsfft_fno_arch* arch, int 
   f->wblk = wgrad_blocks(max_batch, f->V);
   f->nchunk = 64;
   const size_t wpart = std::max((size_t)f->wblk * (32 * 32 + 32),
-                                (size_t)project_bwd_blocks(max_batch, f->V) * (65 * H + 32));
+                                (size_t)project_bwd_blocks(max_batch, f->V, arch->hidden) * (65 * H + 32));
   ok = ok && alloc(f, &f->y, B * (size_t)arch->cout * V) && alloc(f, &f->dy, B * (size_t)arch->cout * V) &&
        alloc(f, &f->sbuf, B * C * V) && alloc(f, &f->dbuf[0], B * C * V) && alloc(f, &f->dbuf[1], B * C * V) &&
        alloc(f, &f->ym, ns * B * C) && alloc(f, &f->gm, ns * B * C) && alloc(f, &f->tw, (size_t)n) &&

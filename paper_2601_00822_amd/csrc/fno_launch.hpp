@@ -66,7 +66,7 @@ struct ProjBwdArgs {
   int hidden, O, opad16, B;
   long long V;
 };
-int project_bwd_blocks(int B, long long V);
+int project_bwd_blocks(int B, long long V, int hidden);
 hipError_t launch_project_bwd(const ProjBwdArgs& a, float* gw1, float* gb1, float* gw2, float* gb2, hipStream_t s);
 
 // The kept modes of a batch are laid out in groups of eight,
