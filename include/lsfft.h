@@ -432,7 +432,16 @@ lsfft_status lsfft_iteration_bytes(lsfft_plan_t p, int grid_idx, int kernel_clas
  * the pencils; y pass: default, twice the pencils, the other radix order; x
  * pass: default, row tiles of half the entries, the other radix order).
  * Every variant computes the same transforms; results differ only by
- * rounding order.
+ * rounding order.  FP32 y passes of 256 points default to variant 1 on grids
+ * with nz nx / 2 >= 4096 (the same bits as variant 0).
+ *
+ * On FP32 3D grids with nx and ny in {32, 48, 64, 96, 128}, except those of
+ * few large planes, an iteration's y, x and y passes are one launch over
+ * whole planes while both passes' variants are 0 (the same bits as those
+ * variants).  Choosing another x or y variant, by lsfft_schedule_set or a
+ * cache entry, runs the passes with it.  lsfft_autotune times both ways and
+ * keeps the faster for each grid, until a later lsfft_schedule_set of its x
+ * or y pass.  Plans with LSFFT_TIMING always run the passes.
  *
  * Kind 3 is the spectral layout of one grid, `len` being the grid's index
  * in the plan: variant 0 keeps the spectra in rows of nx/2 entries
@@ -453,12 +462,14 @@ typedef struct {
   int variant;
   int chosen;     /* 1 for the variant the plan now uses */
   double us;      /* mean kernel time per launch in microseconds, summed over the plan's grids sharing that length;
-                     kind 3: kernel time of the x, y and outer passes per iteration of the tuning batch */
+                     kind 3: kernel time of the x, y and outer passes per iteration of the tuning batch (the
+                     launch over whole planes in the x and y passes' place where it is faster) */
 } lsfft_tune_entry;
 
 /* Current variant and number of variants of one pass of the plan's 3D (or
  * 2D) grids on an axis of `len` points (kind 3: of the layout of grid
- * `len`, whose dimension must be `dim`).  LSFFT_E_ARG for a bad kind,
+ * `len`, whose dimension must be `dim`); where a default differs from grid
+ * to grid, the largest.  LSFFT_E_ARG for a bad kind,
  * dimension, unsupported length or grid index. */
 lsfft_status lsfft_schedule_get(lsfft_plan_t p, int dim, int kind, int len, int* variant, int* nvariants);
 
@@ -477,13 +488,15 @@ lsfft_status lsfft_schedule_set(lsfft_plan_t p, int dim, int kind, int len, int 
  * variant round with every launch timed by a HIP event pair; each pass kind
  * is judged by its own mean kernel time per launch.  A grid that has two
  * spectral layouts runs its rounds under each; it keeps the layout whose
- * fastest variants give the smaller kernel time of the x, y and outer
- * passes per iteration, and the variants are chosen on the times under the
+ * fastest variants (or the launch over whole planes) give the smaller kernel
+ * time per iteration, and the variants are chosen on the times under the
  * chosen layouts.  The plan's own precision and scheme are used (FP32 inner
  * solves for LSFFT_REFINE64).
  *  cache_path  NULL, or a file to merge the choices into: a flat JSON object
  *              {"f32/3d/outer/256": 2, "f32/3d/layout/256x256x256": 1, ...}
- *              (layouts keyed by nx x ny x nz); lsfft_plan reads the file
+ *              (layouts keyed by nx x ny x nz, and so "f32/3d/plane/...": 1
+ *              where whole planes in one launch beat the x and y passes);
+ *              lsfft_plan reads the file
  *              named by the environment variable LSFFT_TUNE_CACHE and applies
  *              the entries matching its grids
  *  out         host [max_out] or NULL: every variant timed (kind, length,

@@ -159,6 +159,10 @@ struct lsfft_plan_s {
   lsfft_plan_s() {
     for (auto& kind : sched) std::fill(kind, kind + kNumLens, -1);
   }
+  // whole planes in one launch per grid (index into grids): 1 always, 0 never, -1 not
+  // chosen: while the x and y passes' variants are the default (takes_plane)
+  std::vector<int> plane;
+  int tune_plane = -1;   // lsfft_autotune: 0 the passes, 1 the plane launch, whatever is chosen
   // spectral layout per grid (index into grids): 1 kx-blocked between the y
   // and outer passes where the grid allows it, 0 rows throughout
   std::vector<int> layout;
@@ -312,6 +316,16 @@ bool geometry(bool f64, const lsfft_grid& g, const int sched[3][kNumLens], Geome
   return true;
 }
 
+// Geometry of the plan's grid gi, with lds_p 0 unless its iterations transform whole
+// planes in one launch.  Timed plans keep one launch per pass, which is what they time.
+bool grid_geometry(const lsfft_plan_s* p, int gi, Geometry* o) {
+  if (!geometry(p->f64, p->grids[gi], p->sched, o, p->layout[gi])) return false;
+  const bool chosen = p->plane[gi] == 1 || (p->plane[gi] < 0 && o->var_x == 0 && o->var_y == 0);
+  const bool take = p->tune_plane >= 0 ? p->tune_plane == 1 : chosen && !(p->flags & LSFFT_TIMING);
+  if (!take) o->lds_p = 0;
+  return true;
+}
+
 // -------------------------------------------------------------------------
 // timing helpers
 // -------------------------------------------------------------------------
@@ -377,7 +391,6 @@ struct Batch {
   std::vector<Seg> segs[L_NUM];   // per list: one segment per (dim, transform length)
   int nseg_total = 0;
   int n_running = 0;
-  bool plane = false;   // iterate eligible solves with k_plane in place of the y, x and y passes
   double tol = 1e-8;
   int max_iter = 0;
   bool averaging = false;
@@ -460,12 +473,11 @@ LaunchArgs base_args(Batch& b) {
 void list_key(const Batch& b, int l, int i, int* dim, int* len, int* items, size_t* lds, int* var) {
   const Geometry& g = b.geo[i];
   *dim = g.dim;
-  const size_t plane = b.plane ? g.lds_p : 0;
   switch (l) {
-    case L_X: *len = g.nx; *items = plane ? 0 : g.items_x; *lds = g.lds_xi; *var = g.var_x; break;
+    case L_X: *len = g.nx; *items = g.lds_p ? 0 : g.items_x; *lds = g.lds_xi; *var = g.var_x; break;
     // one key for the two lengths; two work items (normal strains, shears) per plane
-    case L_P: *len = g.nx << 16 | g.ny; *items = plane ? 2 * g.nz : 0; *lds = plane; *var = 0; break;
-    case L_Y: *len = g.ny; *items = plane ? 0 : g.items_y; *lds = g.lds_y; *var = g.var_y; break;
+    case L_P: *len = g.nx << 16 | g.ny; *items = g.lds_p ? 2 * g.nz : 0; *lds = g.lds_p; *var = 0; break;
+    case L_Y: *len = g.ny; *items = g.lds_p ? 0 : g.items_y; *lds = g.lds_y; *var = g.var_y; break;
     case L_XALL: *len = g.nx; *items = g.items_xall; *lds = g.lds_x; *var = g.var_x; break;
     case L_XLEAD: *len = g.nx; *items = g.items_xft; *lds = g.lds_x; *var = g.var_x; break;
     case L_YALL: case L_YLEAD: *len = g.ny; *items = g.items_y; *lds = g.lds_y; *var = g.var_y; break;
@@ -599,16 +611,13 @@ lsfft_status prepare(Batch& b, bool validate = true) {
   const bool cg = p->scheme == LSFFT_CG || p->scheme == LSFFT_CG_PLAIN;
 
   if (host_fence(p) != LSFFT_OK) return LSFFT_E_DEVICE;
-  // timed plans and autotuning keep one launch per pass, which is what they time
-  // (the iterates are the same bit for bit)
-  b.plane = (p->flags & LSFFT_TIMING) == 0 && !p->force_timing;
   // geometry, Lame tables
   b.geo.resize(n);
   b.desc.assign(n, InstDesc{});
   b.state.assign(n, InstState{});
   b.lame.clear();
   for (int i = 0; i < n; ++i) {
-    if (!geometry(f64, p->grids[b.specs[i].grid], p->sched, &b.geo[i], p->layout[b.specs[i].grid])) return LSFFT_E_ARG;
+    if (!grid_geometry(p, b.specs[i].grid, &b.geo[i])) return LSFFT_E_ARG;
   }
 
   // workspace layout
@@ -653,7 +662,7 @@ lsfft_status prepare(Batch& b, bool validate = true) {
     const Geometry& g = b.geo[i];
     list_need[L_X] += g.items_x; list_need[L_Y] += g.items_y; list_need[L_G] += g.items_g;
     list_need[L_CG] += g.items_cg;
-    if (b.plane && g.lds_p) list_need[L_P] += 2 * g.nz;
+    if (g.lds_p) list_need[L_P] += 2 * g.nz;
   }
   if (list_need[L_X] == 0) list_need[L_X] = 1;
   list_need[L_XALL] = list_need[L_XLEAD] = 0;
@@ -827,7 +836,8 @@ hipError_t pass_y(Batch& b, int list, int dir, int which, int ncomp, int gate, i
 hipError_t pass_yxy(Batch& b, bool reduce) {
   for (const Seg& sg : b.segs[L_P]) {
     if (sg.count == 0) continue;
-    LaunchArgs a = largs(b, L_P, sg);
+    const int t = timed_begin(b.p, LSFFT_K_XPASS);
+    LaunchArgs a = timed(b.p, largs(b, L_P, sg), t);
     if (reduce) {
       a.red_inst = b.d_inst;
       a.red_n = b.d_counts + kMaxSegs - 1;
@@ -1413,6 +1423,13 @@ std::string layout_key(bool f64, const lsfft_grid& g) {
   return buf;
 }
 
+// ... and of its choice between the plane launch and the passes
+std::string plane_key(const lsfft_grid& g) {
+  char buf[96];
+  std::snprintf(buf, sizeof buf, "f32/3d/plane/%lldx%lldx%lld", (long long)gnx(g), (long long)gny(g), (long long)gnz(g));
+  return buf;
+}
+
 bool same_shape(const lsfft_grid& a, const lsfft_grid& b) {
   return a.dim == b.dim && gnx(a) == gnx(b) && gny(a) == gny(b) && gnz(a) == gnz(b);
 }
@@ -1429,6 +1446,11 @@ void apply_tune_cache(lsfft_plan_s* p, const std::map<std::string, int>& m) {
     if (!blocked_layout_ok(p->grids[gi])) continue;
     const auto it = m.find(layout_key(p->f64, p->grids[gi]));
     if (it != m.end() && it->second <= 1) set_layout(p, (int)gi, it->second);
+  }
+  for (size_t gi = 0; gi < p->grids.size(); ++gi) {
+    if (p->f64 || p->grids[gi].dim != 3) continue;
+    const auto it = m.find(plane_key(p->grids[gi]));
+    if (it != m.end() && it->second <= 1) p->plane[gi] = it->second;
   }
   for (const lsfft_grid& g : p->grids) {
     const int lens[3] = {(int)gnx(g), (int)gny(g), (int)(g.dim == 3 ? gnz(g) : gny(g))};
@@ -1592,6 +1614,7 @@ lsfft_status lsfft_plan(lsfft_plan_t* out, const lsfft_grid* grids, int ngrid, i
   // are half a kx block wide, start in rows (at 128^3: 21.0 against 23.9 ms
   // per solve)
   p->layout.assign(p->grids.size(), p->f64 ? 0 : 1);
+  p->plane.assign(p->grids.size(), -1);
   p->max_batch = max_batch;
   // schedule variants chosen by an earlier lsfft_autotune, if a cache is named
   if (const char* path = std::getenv("LSFFT_TUNE_CACHE")) {
@@ -1623,6 +1646,7 @@ lsfft_status lsfft_plan(lsfft_plan_t* out, const lsfft_grid* grids, int ngrid, i
     q->flags = flags & LSFFT_STRICT_EQUIL;   // the force check runs on the FP64 force transform
     q->grids = p->grids;
     q->layout = p->layout;   // the FP64 and FP32 spectra of a solve share one layout
+    q->plane.assign(q->grids.size(), -1);
     q->max_batch = p->max_batch;
     p->sub = q;
     if (!upload_twiddles(q)) {
@@ -1915,7 +1939,7 @@ lsfft_status lsfft_iteration_bytes(lsfft_plan_t p, int grid_idx, int kernel_clas
   if (!p || !bytes || grid_idx < 0 || grid_idx >= (int)p->grids.size()) return LSFFT_E_ARG;
   if (kernel_class < 0 || kernel_class >= LSFFT_K_COUNT) return LSFFT_E_ARG;
   Geometry g;
-  if (!geometry(p->f64, p->grids[grid_idx], p->sched, &g, p->layout[grid_idx])) return LSFFT_E_ARG;
+  if (!grid_geometry(p, grid_idx, &g)) return LSFFT_E_ARG;
   const double comp = (double)g.Pm * (p->f64 ? 16.0 : 8.0);  // one complex half-spectrum stream
   const double s = g.s, d = g.dim;
   const bool cg = p->scheme == LSFFT_CG || p->scheme == LSFFT_CG_PLAIN;
@@ -1923,9 +1947,9 @@ lsfft_status lsfft_iteration_bytes(lsfft_plan_t p, int grid_idx, int kernel_clas
   switch (kernel_class) {
     case LSFFT_K_XPASS: b = 2 * s * comp + (double)g.nvox; break;          // eps^ in, sigma^ out, phase
     case LSFFT_K_YPASS:
-      // two sweeps, in and out; none where k_plane does them in the x pass's place
-      // (timed plans keep the passes)
-      b = (g.dim == 3 && !(g.lds_p && !(p->flags & LSFFT_TIMING))) ? 4 * s * comp : 0.0;
+      // two sweeps, in and out; none where the plane launch, which takes the x pass's
+      // place, does them
+      b = (g.dim == 3 && !g.lds_p) ? 4 * s * comp : 0.0;
       break;
     case LSFFT_K_GREEN:
       if (p->scheme == LSFFT_ANDERSON) {
@@ -1958,7 +1982,14 @@ lsfft_status lsfft_schedule_get(lsfft_plan_t p, int dim, int kind, int len, int*
     return LSFFT_OK;
   }
   if (!p || (dim != 2 && dim != 3) || kind < 0 || kind > 2 || len_index(len) < 0) return LSFFT_E_ARG;
-  if (variant) *variant = plan_variant(p->sched, p->f64, dim, kind, len);
+  int v = plan_variant(p->sched, p->f64, dim, kind, len);
+  // a default that depends on the grid (geometry): the largest of the plan's grids
+  if (dim == 3 && kind == 1)
+    for (size_t gi = 0; gi < p->grids.size(); ++gi) {
+      Geometry g;
+      if (p->grids[gi].dim == 3 && gny(p->grids[gi]) == len && grid_geometry(p, (int)gi, &g)) v = std::max(v, g.var_y);
+    }
+  if (variant) *variant = v;
   if (nvariants) *nvariants = schedule_variants(p->f64, dim, kind, len);
   return LSFFT_OK;
 }
@@ -1972,7 +2003,13 @@ lsfft_status lsfft_schedule_set(lsfft_plan_t p, int dim, int kind, int len, int 
   }
   if (!p || (dim != 2 && dim != 3) || kind < 0 || kind > 2 || len_index(len) < 0) return LSFFT_E_ARG;
   if (variant < 0 || variant >= schedule_variants(p->f64, dim, kind, len)) return LSFFT_E_ARG;
-  if (dim == 3) p->sched[kind][len_index(len)] = variant;   // 2D grids have the default only
+  if (dim != 3) return LSFFT_OK;   // 2D grids have the default only
+  p->sched[kind][len_index(len)] = variant;
+  // an earlier choice of the plane launch or the passes gives way to this one
+  for (size_t gi = 0; gi < p->grids.size(); ++gi) {
+    const lsfft_grid& g = p->grids[gi];
+    if (g.dim == 3 && kind < 2 && len == (kind == 0 ? gnx(g) : gny(g))) p->plane[gi] = -1;
+  }
   return LSFFT_OK;
 }
 
@@ -2099,6 +2136,15 @@ lsfft_status lsfft_autotune(lsfft_plan_t p, int iters, const char* cache_path, l
   struct GridTimes {
     int nl = 1, lay[2] = {0, 0}, nv[3] = {1, 1, 1}, lens[3] = {0, 0, 0}, rounds = 1;
     std::vector<std::array<double, 3>> ms[2];
+    bool plane = false;                 // the grid's planes fit one launch: its ms
+    double plane_ms[2] = {0.0, 0.0};
+    // fastest x and y passes under layout l, and whether the plane launch beats them
+    double best(int l, int k) const {
+      double b = ms[l][0][k];
+      for (int r = 1; r < nv[k]; ++r) b = std::min(b, ms[l][r][k]);
+      return b;
+    }
+    bool take(int l) const { return plane && plane_ms[l] < best(l, 0) + best(l, 1); }
   };
   std::vector<GridTimes> gt(tg.size());
   for (size_t ti = 0; ti < tg.size(); ++ti) {
@@ -2115,9 +2161,11 @@ lsfft_status lsfft_autotune(lsfft_plan_t p, int iters, const char* cache_path, l
     const bool two = blocked_layout_ok(g);
     G.nl = two ? 2 : 1;
     G.lay[0] = two ? 1 : p->layout[t.gi];
+    G.plane = !(p->flags & LSFFT_TIMING) && plane_lds(p->f64, G.lens[0], G.lens[1], G.lens[2]) > 0;
     int keep[3];
     for (int k = 0; k < 3; ++k) keep[k] = p->sched[k][len_index(G.lens[k])];
     lsfft_status ls = LSFFT_OK;
+    p->tune_plane = 0;
     for (int l = 0; l < G.nl && ls == LSFFT_OK; ++l) {
       for (size_t gj = 0; gj < p->grids.size(); ++gj)
         if (same_shape(p->grids[gj], g)) set_layout(p, (int)gj, G.lay[l]);
@@ -2127,14 +2175,22 @@ lsfft_status lsfft_autotune(lsfft_plan_t p, int iters, const char* cache_path, l
         if ((ls = time_grid(t)) != LSFFT_OK) break;
         for (int k = 0; k < 3; ++k) G.ms[l][r][k] = p->kt_ms[cls[k]] / iters;
       }
+      if (ls == LSFFT_OK && G.plane) {
+        p->tune_plane = 1;
+        ls = time_grid(t);
+        p->tune_plane = 0;
+        G.plane_ms[l] = p->kt_ms[LSFFT_K_XPASS] / iters;
+      }
     }
+    p->tune_plane = -1;
     for (int k = 0; k < 3; ++k) p->sched[k][len_index(G.lens[k])] = keep[k];
     lsfft_kernel_times_reset(p);
     if (ls != LSFFT_OK) return ls;
   }
   // Layout per grid: the smaller kernel time of the three passes per
-  // iteration, each pass on its fastest variant under that layout (ties go
-  // to the blocked layout).
+  // iteration, each pass on its fastest variant under that layout, the x and y
+  // passes' replaced by the plane launch's where that is smaller (ties go to the
+  // blocked layout).
   std::map<std::string, int> chosen;
   std::vector<int> li(tg.size(), 0);
   int n = 0;
@@ -2144,14 +2200,14 @@ lsfft_status lsfft_autotune(lsfft_plan_t p, int iters, const char* cache_path, l
     const lsfft_grid& g = p->grids[tg[ti].gi];
     double cost[2] = {0.0, 0.0};
     for (int l = 0; l < G.nl; ++l)
-      for (int k = 0; k < 3; ++k) {
-        double best = G.ms[l][0][k];
-        for (int r = 1; r < G.nv[k]; ++r) best = std::min(best, G.ms[l][r][k]);
-        cost[l] += best;
-      }
+      cost[l] = (G.take(l) ? G.plane_ms[l] : G.best(l, 0) + G.best(l, 1)) + G.best(l, 2);
     li[ti] = (G.nl == 2 && cost[1] < cost[0]) ? 1 : 0;
     for (size_t gj = 0; gj < p->grids.size(); ++gj)
-      if (same_shape(p->grids[gj], g)) set_layout(p, (int)gj, G.lay[li[ti]]);
+      if (same_shape(p->grids[gj], g)) {
+        set_layout(p, (int)gj, G.lay[li[ti]]);
+        if (G.plane) p->plane[gj] = G.take(li[ti]);
+      }
+    if (G.plane) chosen[plane_key(g)] = G.take(li[ti]);
     if (G.nl == 2) {
       chosen[layout_key(p->f64, g)] = G.lay[li[ti]];
       for (int l = 0; l < 2; ++l)
@@ -2159,12 +2215,18 @@ lsfft_status lsfft_autotune(lsfft_plan_t p, int iters, const char* cache_path, l
     }
   }
   // Variant per (kind, length): mean kernel time per launch, summed over the
-  // grids sharing that length, each under its chosen layout.
+  // grids sharing that length, each under its chosen layout.  A grid that takes the
+  // plane launch has no say in the x and y passes of one that runs them.
   std::map<std::pair<int, int>, std::vector<double>> times;
+  std::map<std::pair<int, int>, bool> run;
+  for (size_t ti = 0; ti < tg.size(); ++ti)
+    for (int k = 0; k < 2; ++k)
+      if (!gt[ti].take(li[ti])) run[{k, gt[ti].lens[k]}] = true;
   for (size_t ti = 0; ti < tg.size(); ++ti) {
     const GridTimes& G = gt[ti];
     for (int k = 0; k < 3; ++k) {
       if (G.nv[k] == 1) continue;   // passes with the default only are not tuned
+      if (k < 2 && G.take(li[ti]) && run.count({k, G.lens[k]})) continue;
       auto& v = times[{k, G.lens[k]}];
       if ((int)v.size() < G.nv[k]) v.resize(G.nv[k], 0.0);
       for (int r = 0; r < G.nv[k]; ++r) v[r] += 1e3 * G.ms[li[ti]][r][k] / per_iter[k];

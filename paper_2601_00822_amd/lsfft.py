@@ -622,7 +622,8 @@ class Plan:
         their spectral layouts, keep the faster layout per grid and the
         fastest variants under it; returns the timings as a list of dicts
         (layout entries: kind "layout", len = the grid's index, us = kernel
-        time of the three passes per iteration on their fastest variants)."""
+        time of the three passes per iteration on their fastest variants,
+        or of whole planes in one launch and the outer pass)."""
         cap = 512
         out = (TuneEntry * cap)()
         n = C.c_int()
