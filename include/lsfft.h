@@ -419,7 +419,13 @@ lsfft_status lsfft_kernel_times(lsfft_plan_t p, int kernel_class, double* total_
 lsfft_status lsfft_kernel_times_reset(lsfft_plan_t p);
 
 /* Algorithmic HBM bytes that one iteration of one solve on grid grid_idx
- * moves in each kernel class (complex half-spectrum streams and phase map). */
+ * moves in each kernel class (complex half-spectrum streams and phase map),
+ * by the kernels that the plan runs: where one launch transforms whole planes
+ * the x class stands for it and the y class is 0; 2D basic-scheme solves that
+ * one workgroup iterates (both axes in {16, 24, 32, 48, 64, 96, 128, 256} and
+ * at most 4096 points) move the state and the force alone, in the outer
+ * class.  Such solves keep the launches under LSFFT_TIMING, in FP32 averages,
+ * and in a batch with a solve that does not qualify. */
 lsfft_status lsfft_iteration_bytes(lsfft_plan_t p, int grid_idx, int kernel_class, double* bytes);
 
 /*

@@ -918,17 +918,22 @@ lsfft_status read_states(Batch& b, std::vector<int>& running) {
   return LSFFT_OK;
 }
 
-// LDS bytes of the one-workgroup-per-solve kernel when every solve of the batch
-// can take it (2D, basic scheme, up to 4096 points: above, a solve's launches are
-// faster than one CU, see k_solve2d.hip), else 0.
+// LDS bytes of the kernel that iterates a whole solve on grid g in one workgroup (2D,
+// basic scheme, up to 4096 points: above, a solve's launches are faster than one CU,
+// see k_solve2d.hip), else 0.  Timed plans keep one launch per pass, which is what
+// they time.
+size_t solve2d_grid(const lsfft_plan_s* p, const Geometry& g, int nphase) {
+  if (p->scheme != LSFFT_BASIC || g.dim != 2 || (p->flags & LSFFT_TIMING) != 0 || p->force_timing) return 0;
+  return solve2d_lds(p->f64, g.nx, g.ny, nphase);
+}
+
+// The same for a batch: when every solve of it can take that kernel.
 size_t fits_solve2d(const Batch& b) {
-  if (b.p->scheme != LSFFT_BASIC) return 0;
   // FP64 sums of FP32 fields keep their digits: there the launches' roundings stay
   if (b.sums32 || (!b.p->f64 && b.averaging)) return 0;
   size_t lds = 0;
   for (size_t i = 0; i < b.specs.size(); ++i) {
-    const Geometry& g = b.geo[i];
-    const size_t need = g.dim == 2 ? solve2d_lds(b.p->f64, g.nx, g.ny, b.specs[i].tab->nphase) : 0;
+    const size_t need = solve2d_grid(b.p, b.geo[i], b.specs[i].tab->nphase);
     if (need == 0) return 0;
     lds = std::max(lds, need);
   }
@@ -943,8 +948,7 @@ lsfft_status iterate(Batch& b, int max_rounds = 0, std::vector<int>* running_out
   const bool cg = p->scheme == LSFFT_CG || p->scheme == LSFFT_CG_PLAIN;
   hipStream_t st = p->stream;
   const bool timing = (p->flags & LSFFT_TIMING) != 0 || p->force_timing;
-  // timed plans keep one launch per pass, which is what they time
-  if (const size_t lds = timing ? 0 : fits_solve2d(b)) {
+  if (const size_t lds = fits_solve2d(b)) {
     p->timing_active = false;
     std::vector<int> running;
     const int steps = max_rounds > 0 ? max_rounds : kSolve2dSteps;
@@ -1943,6 +1947,12 @@ lsfft_status lsfft_iteration_bytes(lsfft_plan_t p, int grid_idx, int kernel_clas
   const double comp = (double)g.Pm * (p->f64 ? 16.0 : 8.0);  // one complex half-spectrum stream
   const double s = g.s, d = g.dim;
   const bool cg = p->scheme == LSFFT_CG || p->scheme == LSFFT_CG_PLAIN;
+  // one workgroup's solve: the strain spectra and the residual sums stay in LDS
+  const bool lds = solve2d_grid(p, g, kMaxPhases) > 0;
+  if (lds) {
+    *bytes = kernel_class == LSFFT_K_GREEN ? 3 * d * comp : 0.0;   // u^, f^ in; u^ out
+    return LSFFT_OK;
+  }
   double b = 0.0;
   switch (kernel_class) {
     case LSFFT_K_XPASS: b = 2 * s * comp + (double)g.nvox; break;          // eps^ in, sigma^ out, phase
