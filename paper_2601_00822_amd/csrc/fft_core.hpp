@@ -192,6 +192,13 @@ __device__ __forceinline__ void bfly(T* vr, T* vi) {
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
+// Orders one wave's LDS accesses, by which its lanes hand data to each other (no other
+// wave is waited for).  The fence alone would order memory but not the lanes: it is no
+// convergent operation, so the compiler could run one side of a branch past it first.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 template <bool LB> __device__ __forceinline__ void tile_sync() {
   if constexpr (LB) lds_barrier();
   else __syncthreads();

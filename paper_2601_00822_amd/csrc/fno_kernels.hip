@@ -35,11 +35,7 @@ __device__ __forceinline__ void gelu_both(float x, float& z, float& g) {
   g = 0.5f * (1.0f + e) + x * 0.39894228040143267794f * expf(-0.5f * x * x);
 }
 
-// order the LDS accesses of one wave (no barrier: other waves are not waited for)
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
+using lsfft::wave_order;
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);

@@ -33,9 +33,6 @@ namespace {
 
 template <typename T> using V2 = T __attribute__((ext_vector_type(2)));
 
-// orders a wave's own LDS accesses
-__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 // a b, rounded as in the other passes
 __device__ __forceinline__ void cmul_fma(float& ar, float& ai, float br, float bi) {
   const float t = __builtin_fmaf(ar, br, -(ai * bi));
@@ -130,16 +127,16 @@ struct WaveFft {
                                              const V2<T>* tw, int lane) {
     static_assert(np == 2 || np == 3, "two or three passes");
     compute<0>(ir, ii, tw, lane);
-    wave_fence();
+    wave_order();
     scatter<0>(ir, ii, z, base, lane);
-    wave_fence();
+    wave_order();
     if constexpr (np == 3) {
       T mr[bpt<1>()][S::r(1)], mi[bpt<1>()][S::r(1)];
       gather<1>(mr, mi, z, base, lane);
       compute<1>(mr, mi, tw, lane);
-      wave_fence();
+      wave_order();
       scatter<1>(mr, mi, z, base, lane);
-      wave_fence();
+      wave_order();
     }
     gather<np - 1>(o_r, o_i, z, base, lane);
     compute<np - 1>(o_r, o_i, tw, lane);
@@ -150,7 +147,7 @@ struct WaveFft {
     T ir[bpt<0>()][S::r(0)], ii[bpt<0>()][S::r(0)], o_r[bpt<np - 1>()][S::r(np - 1)], o_i[bpt<np - 1>()][S::r(np - 1)];
     gather<0>(ir, ii, z, base, lane);
     run(ir, ii, o_r, o_i, z, base, tw, lane);
-    wave_fence();
+    wave_order();
     scatter<np - 1>(o_r, o_i, z, base, lane);
   }
 };
@@ -421,10 +418,10 @@ __device__ __forceinline__ void plane_item(const InstDesc& D, int local, const T
       constexpr int PL = XF::S::r(XF::np - 1), BL = XF::template bpt<XF::np - 1>();
       T zr[BL][PL], zi[BL][PL];
       XF::run(vr, vi, zr, zi, z, row, twx, lane);
-      wave_fence();
+      wave_order();
       XF::template scatter<XF::np - 1>(zr, zi, z, row, lane);
     }
-    wave_fence();
+    wave_order();
     // unfold in place, the pair (k, H - k) by one lane; 0 goes with H / 2
     constexpr int UN = C::RW * (H / 2);
     constexpr bool same = 64 % (H / 2) == 0;   // a lane's pairs: the same in rows 128 / H apart

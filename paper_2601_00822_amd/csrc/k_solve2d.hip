@@ -48,9 +48,6 @@ constexpr int kPoints2d = 4096;
 
 template <typename T> using V2 = T __attribute__((ext_vector_type(2)));
 
-// orders a wave's own LDS accesses
-__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 // Passes of a length-N transform of all components of the MP pencils that a wave
 // owns.  `at` maps (component, pencil, index) to an LDS word.
 //  JF: index-fastest butterflies (x), else pencil-fastest (y)
@@ -171,16 +168,16 @@ struct Fft3 {
           o_i[q][r] = ii[q][r];
         }
     } else {
-      wave_fence();
+      wave_order();
       scatter<0>(ir, ii, z, at, npen, tid);
-      wave_fence();
+      wave_order();
       if constexpr (np == 3) {
         T mr[bpt<1>()][S::r(1)], mi[bpt<1>()][S::r(1)];
         gather<1>(mr, mi, z, at, npen, tid);
         compute<1>(mr, mi, tw, npen, tid);
-        wave_fence();
+        wave_order();
         scatter<1>(mr, mi, z, at, npen, tid);
-        wave_fence();
+        wave_order();
       }
       gather<np - 1>(o_r, o_i, z, at, npen, tid);
       compute<np - 1>(o_r, o_i, tw, npen, tid);
@@ -264,10 +261,10 @@ __device__ __forceinline__ void x_phase(const Lds<T>& L, int ny) {
     {
       T zr[FF::template bpt<FF::np - 1>()][PL_], zi[FF::template bpt<FF::np - 1>()][PL_];
       FF::run(vr, vi, zr, zi, L.z, at, L.twx, nr, tid);
-      wave_fence();
+      wave_order();
       FF::template scatter<FF::np - 1>(zr, zi, L.z, at, nr, tid);
     }
-    wave_fence();
+    wave_order();
     // unfold in place, the pair (k, H - k) by one lane; 0 goes with H / 2
     for (int e = tid; e < nr * (H / 2); e += 64) {
       const int m = e / (H / 2), k = e - m * (H / 2), kb = k ? H - k : H / 2;
@@ -285,7 +282,7 @@ __device__ __forceinline__ void x_phase(const Lds<T>& L, int ny) {
         L.z[a] = k ? xa : V2<T>{va.x + va.y, va.x - va.y};
       }
     }
-    wave_fence();
+    wave_order();
   }
   lds_barrier();
 }
@@ -365,7 +362,7 @@ __device__ __forceinline__ double y_phase(const Lds<T>& L, const InstDesc& D, in
     }
     T er[FI::template bpt<FI::np - 1>()][PE], ei[FI::template bpt<FI::np - 1>()][PE];
     FI::run(sr, si, er, ei, L.z, at, L.twy, nc, tid);
-    wave_fence();
+    wave_order();
     FI::template scatter<FI::np - 1>(er, ei, L.z, at, nc, tid);
   }
   lds_barrier();
