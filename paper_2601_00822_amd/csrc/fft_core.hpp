@@ -192,6 +192,11 @@ __device__ __forceinline__ void bfly(T* vr, T* vi) {
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
+// What kernels with more than 64 KB of dynamic LDS declare as their most, whatever a
+// launch takes: the limit belongs to the function, so one set to a call's own need
+// could be lowered by another thread's call before this one's launch.
+constexpr int kMaxDynamicLds = 158 * 1024;
+
 // Orders one wave's LDS accesses, by which its lanes hand data to each other (no other
 // wave is waited for).  The fence alone would order memory but not the lanes: it is no
 // convergent operation, so the compiler could run one side of a branch past it first.

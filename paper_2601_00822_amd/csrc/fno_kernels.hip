@@ -52,7 +52,7 @@ template <typename K>
 static hipError_t allow_lds(K kernel, size_t bytes) {
   if (bytes <= 64 * 1024) return hipSuccess;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
+                             lsfft::kMaxDynamicLds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1252,7 +1252,7 @@ static hipError_t cube_n(bool fwd, int M, int BC, const float* h, const float2* 
   a.s1 = s1;
   a.tw = tw;
   const size_t lds = (size_t)N * a.PP * sizeof(float2);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  if (lds > (size_t)lsfft::kMaxDynamicLds) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)(BC < 256 * (N == 32 ? 1 : 4) ? BC : 256 * (N == 32 ? 1 : 4));
   hipError_t e = fwd ? allow_lds(k_cube_fwd<N>, lds) : allow_lds(k_cube_inv<N>, lds);
   if (e != hipSuccess) return e;

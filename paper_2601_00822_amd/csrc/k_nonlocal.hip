@@ -17,6 +17,7 @@
 
 #include <vector>
 
+#include "fft_core.hpp"
 #include "launch.hpp"
 #include "lsfft_internal.hpp"
 
@@ -648,7 +649,7 @@ template <typename K>
 hipError_t allow_lds(K kernel, size_t bytes) {
   if (bytes <= 64 * 1024) return hipSuccess;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
+                             kMaxDynamicLds);
 }
 
 // classes of the scalar form: row(|r|^2) -> weight row of nw doubles; the row of
@@ -808,7 +809,7 @@ hipError_t gram_matrix(int dim, const int n[3], int R, double delta, int deg, in
   lds = std::max(lds, sizeof(double) * (size_t)(NT / 64) * rows * kFPitch);
   lds = std::max(lds, sizeof(double) * (size_t)(NT / 64) * nacc);
   lds += kRowBytes;
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  if (lds > (size_t)kMaxDynamicLds) return hipErrorInvalidValue;
   const int* d_first = t.ints;
   const int* d_offs = t.ints + nshell + 1;
   const double* d_W = t.vals + ev.size();

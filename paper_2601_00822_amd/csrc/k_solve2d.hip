@@ -473,8 +473,9 @@ size_t solve2d_lds(bool f64, int nx, int ny, int nphase) {
 
 hipError_t launch_solve2d(bool f64, const LaunchArgs& a, const int* inst, int count, int steps) {
   if (count <= 0) return hipSuccess;
+  if (a.lds > (size_t)kMaxDynamicLds) return hipErrorInvalidValue;
   const void* k = f64 ? reinterpret_cast<const void*>(k_solve2d<double>) : reinterpret_cast<const void*>(k_solve2d<float>);
-  const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
+  const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynamicLds);
   if (e != hipSuccess) return e;
   if (f64)
     hipLaunchKernelGGL(k_solve2d<double>, dim3((unsigned)count), NT2, a.lds, a.stream, a.desc, a.state, inst, a.lame,
