@@ -578,12 +578,25 @@ Geom pick(int dim, const int n[3], int R, int zv) {
   return 4LL * G.ntA * G.ntB * G.ntC <= 5LL * H.ntA * H.ntB * H.ntC ? G : H;
 }
 
+// compiled feature counts (degree + 1 rounded up: the padded features are
+// zero) and halos
+constexpr int feature_count(int nf) { return nf <= 3 ? 3 : nf <= 5 ? 5 : nf <= 7 ? 7 : 9; }
+
+// a workgroup's partial sums in the matrix form: pairs of 16-row tiles of the features
+// and Gamma
+constexpr int matrix_acc(int nf) { return 2 * nf + 1 <= 16 ? 256 : 3 * 256; }
+
 // Fixed device scratch for a call's tables and work area: allocating and freeing the
-// matrix form's 2 MB took 45 us of the 517 of its two calls at 64^3 (472 now; the
-// scalar form's 0.2 MB cost nothing measurable, 576 and 575).
+// matrix form's 2 MB took 45 us of the 517 of its two calls at 64^3 and degree 6 (472
+// without; the scalar form's 0.2 MB cost nothing measurable, 576 and 575), and 6.3 MB
+// 33 of the 97 us of the normal equations of a 32 x 32 grid at degree 8.  It holds every call
+// that the library takes: the partial sums of the highest degree, and tables (the
+// largest, of the matrix operator at horizon 7 in 3D, 51 KB).
 // A device's copy belongs to one call at a time, which holds it until its stream has
-// drained; a second call meanwhile, or one that needs more, allocates.
-constexpr size_t kScratch = 4u << 20;
+// drained; a second call meanwhile allocates.
+constexpr size_t kSums = sizeof(double) * (kSlots1 + 1) * matrix_acc(feature_count(kNlMaxDegree + 1));
+constexpr size_t kScratch = kSums + (128u << 10);
+static_assert(kSlots * 55 <= kSlots1 * matrix_acc(feature_count(kNlMaxDegree + 1)), "scalar form: 55 sums of nine features");
 __device__ __align__(256) char nl_scratch[kScratch];
 constexpr int kMaxDevices = 64;
 std::atomic<bool> scratch_held[kMaxDevices];
@@ -696,10 +709,6 @@ void bernstein(int M, double delta, int rr, double* w) {
   }
 }
 
-// compiled feature counts (degree + 1 rounded up: the padded features are
-// zero) and halos
-int feature_count(int nf) { return nf <= 3 ? 3 : nf <= 5 ? 5 : nf <= 7 ? 7 : 9; }
-
 template <typename T, int NF>
 hipError_t gram_r(int R, const Geom& G, size_t lds, unsigned grid, hipStream_t st, const void* u, const void* gam,
                   int nsample, const Tables& t, int ncls) {
@@ -730,11 +739,11 @@ hipError_t gram_scalar(int dim, const int n[3], int R, double delta, int deg, in
   std::vector<double> vals;
   int ncls = 0;
   scalar_classes(G, R, delta, NF, [&](int rr, double* w) { bernstein(deg, delta, rr, w); }, ints, vals, ncls);
-  Tables t;
-  hipError_t e = t.upload(ints, vals, (size_t)kSlots * nacc + nacc, st);
-  if (e != hipSuccess) return e;
   const long long items = (long long)nsample * G.ntA * G.ntB * G.ntC;
   const unsigned grid = (unsigned)(items < kSlots ? items : kSlots);
+  Tables t;
+  hipError_t e = t.upload(ints, vals, ((size_t)grid + 1) * nacc, st);
+  if (e != hipSuccess) return e;
   const size_t lds = kRowBytes + std::max(box_bytes(G, sizeof(T)), sizeof(double) * nacc * (NT / 64));
   switch (NF) {
     case 3: e = gram_r<T, 3>(R, G, lds, grid, st, u, gam, nsample, t, ncls); break;
@@ -743,7 +752,7 @@ hipError_t gram_scalar(int dim, const int n[3], int R, double delta, int deg, in
     default: e = gram_r<T, 9>(R, G, lds, grid, st, u, gam, nsample, t, ncls); break;
   }
   if (e != hipSuccess) return e;
-  double* out = t.work + (size_t)kSlots * nacc;
+  double* out = t.work + (size_t)grid * nacc;
   hipLaunchKernelGGL(k_nl_sum, dim3((unsigned)nacc), NT, 0, st, t.work, (int)grid, nacc, out);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   std::vector<double> acc(nacc);
@@ -799,12 +808,12 @@ hipError_t gram_matrix(int dim, const int n[3], int R, double delta, int deg, in
   ints.insert(ints.end(), offs.begin(), offs.end());
   std::vector<double> vals(ev);
   vals.insert(vals.end(), W.begin(), W.end());
-  const int rows = 2 * NF + 1, ntl = rows <= 16 ? 1 : 2, nacc = ntl * (ntl + 1) / 2 * 256;
-  Tables t;
-  hipError_t e = t.upload(ints, vals, (size_t)kSlots1 * nacc + nacc, st);
-  if (e != hipSuccess) return e;
+  const int rows = 2 * NF + 1, nacc = matrix_acc(NF);
   const long long items = (long long)nsample * G.ntA * G.ntB * G.ntC;
   const unsigned grid = (unsigned)(items < kSlots1 ? items : kSlots1);
+  Tables t;
+  hipError_t e = t.upload(ints, vals, ((size_t)grid + 1) * nacc, st);
+  if (e != hipSuccess) return e;
   size_t lds = 3 * box_bytes(G, sizeof(T));
   lds = std::max(lds, sizeof(double) * (size_t)(NT / 64) * rows * kFPitch);
   lds = std::max(lds, sizeof(double) * (size_t)(NT / 64) * nacc);
@@ -828,7 +837,7 @@ hipError_t gram_matrix(int dim, const int n[3], int R, double delta, int deg, in
     default: return hipErrorInvalidValue;
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  double* out = t.work + (size_t)kSlots1 * nacc;
+  double* out = t.work + (size_t)grid * nacc;
   hipLaunchKernelGGL(k_nl_sum, dim3((unsigned)nacc), NT, 0, st, t.work, (int)grid, nacc, out);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   std::vector<double> acc(nacc);
