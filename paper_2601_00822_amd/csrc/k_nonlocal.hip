@@ -136,9 +136,13 @@ __device__ __forceinline__ void stage(const Geom& G, const T* __restrict__ u, co
 // either order in 3D) share every weight, so their sum E along C is formed
 // first, then E(c + dC) + E(c - dC), less u(x) as often as there are offsets in
 // it: subtracted once for the whole horizon instead, the error of a field with a
-// rigid offset was 2 to 24 times larger (horizons 1.5 to 6).  cls[4 k]: columns of class k
-// (first, count), its largest dC, and its first weight row; `col` holds the
-// columns' LDS offsets.  Class 0 is the column of r = 0, which itself is left out.
+// rigid offset was 2 to 24 times larger (horizons 1.5 to 6).  FP32 fields are
+// rounded at 6e-8 of their offset, far above either: there the weight of r = 0 is
+// minus the sum of all others (eight 64^3 fields at horizon 3: the operator in 70
+// us against 81).  cls[4 k]: columns of class k (first, count), its largest dC, and
+// its first weight row; `col` holds the columns' LDS offsets.  Class 0 is the column
+// of r = 0.
+template <typename T> constexpr bool by_class() { return sizeof(T) == 8; }
 template <typename T, int R, int DIM, int ZV>
 __device__ __forceinline__ void column_sums(const T* lds, int base, const int* __restrict__ col, int n,
                                             double (&E)[ZV + 2 * R]) {
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(NT) void k_nl_gram(Geom G, const T* __restrict__ u,
       double phi[ZV][NF], u0[ZV];
 #pragma unroll
       for (int v = 0; v < ZV; ++v) {
-        u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
+        if (by_class<T>()) u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
 #pragma unroll
         for (int m = 0; m < NF; ++m) phi[v][m] = 0.0;
       }
@@ -210,11 +214,12 @@ __global__ __launch_bounds__(NT) void k_nl_gram(Geom G, const T* __restrict__ u,
 #pragma unroll
         for (int d = 0; d <= R; ++d) {
           if (d > zr) break;
-          if (d == 0 && q == 0) continue;
+          if (by_class<T>() && d == 0 && q == 0) continue;
           const double n = double(d ? 2 * cn : cn);
 #pragma unroll
           for (int v = 0; v < ZV; ++v) {
-            const double D = __builtin_fma(-n, u0[v], d ? E[v + R + d] + E[v + R - d] : E[v + R]);
+            double D = d ? E[v + R + d] + E[v + R - d] : E[v + R];
+            if (by_class<T>()) D = __builtin_fma(-n, u0[v], D);
 #pragma unroll
             for (int m = 0; m < NF; ++m) phi[v][m] += w[d * NF + m] * D;
           }
@@ -280,7 +285,7 @@ __global__ __launch_bounds__(NT) void k_nl_apply(Geom G, const T* __restrict__ u
 #pragma unroll
     for (int v = 0; v < ZV; ++v) {
       r[v] = 0.0;
-      u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
+      if (by_class<T>()) u0[v] = double(lds[s.base + (v + R) * Pitch<R, DIM>::C]);
     }
     for (int q = 0; q < ncls; ++q) {
       const int c0 = cls[4 * q], cn = cls[4 * q + 1], zr = cls[4 * q + 2];
@@ -290,11 +295,14 @@ __global__ __launch_bounds__(NT) void k_nl_apply(Geom G, const T* __restrict__ u
 #pragma unroll
       for (int d = 0; d <= R; ++d) {
         if (d > zr) break;
-        if (d == 0 && q == 0) continue;
+        if (by_class<T>() && d == 0 && q == 0) continue;
         const double n = double(d ? 2 * cn : cn);
 #pragma unroll
-        for (int v = 0; v < ZV; ++v)
-          r[v] += w[d] * __builtin_fma(-n, u0[v], d ? E[v + R + d] + E[v + R - d] : E[v + R]);
+        for (int v = 0; v < ZV; ++v) {
+          double D = d ? E[v + R + d] + E[v + R - d] : E[v + R];
+          if (by_class<T>()) D = __builtin_fma(-n, u0[v], D);
+          r[v] += w[d] * D;
+        }
       }
     }
 #pragma unroll
@@ -666,11 +674,12 @@ hipError_t allow_lds(K kernel, size_t bytes) {
 }
 
 // classes of the scalar form: row(|r|^2) -> weight row of nw doubles; the row of
-// r = 0 is not used
+// r = 0 (FP32 fields) is minus the sum of all the others over the horizon
 template <typename Fn>
 void scalar_classes(const Geom& G, int R, double delta, int nw, Fn&& row, std::vector<int>& ints,
                     std::vector<double>& vals, int& ncls) {
   std::vector<int> cls, col;
+  std::vector<double> total(nw, 0.0);
   const bool three = G.dim == 3;
   auto inside = [&](int rr) { return std::sqrt((double)rr) < delta; };
   for (int p = 0; p <= R; ++p)
@@ -691,9 +700,12 @@ void scalar_classes(const Geom& G, int R, double delta, int nw, Fn&& row, std::v
       for (int d = 0; d <= zr; ++d) {
         const size_t at = vals.size();
         vals.resize(at + nw, 0.0);
-        if (p || q || d) row(p * p + q * q + d * d, &vals[at]);
+        if (!p && !q && !d) continue;   // the first row, filled below
+        row(p * p + q * q + d * d, &vals[at]);
+        for (int m = 0; m < nw; ++m) total[m] += vals[at + m] * n * (d ? 2 : 1);
       }
     }
+  for (int m = 0; m < nw; ++m) vals[m] = -total[m];
   ncls = (int)cls.size() / 4;
   ints = cls;
   ints.insert(ints.end(), col.begin(), col.end());

@@ -114,3 +114,18 @@ def test_normal_equations(form):
     Gw, gw, ggw = N.normal_equations([u], [gam], deg, delta, form)
     np.testing.assert_allclose(G, Gw, rtol=0, atol=1e-10 * np.abs(Gw).max())
     np.testing.assert_allclose(g, gw, rtol=0, atol=1e-10 * np.abs(Gw).max() ** 0.5 * ggw ** 0.5)
+
+
+@pytest.mark.parametrize("form", [0, 1])
+def test_fp32_fields(form):
+    # one rounding to FP32 (6e-8) of the largest value; sums in FP64 add some 1e-16 of
+    # the offset, 1e4, per term
+    torch = torch_gpu()
+    from paper_2601_00822_amd import nonlocal_apply
+    shape, delta, deg = (9, 12, 33), 4.0, 5
+    say(f"FP32 fields {shape} form {form}")
+    c = np.random.default_rng(deg).normal(size=(form + 1) * (deg + 1))
+    u = field(shape, 7, 1e-2).astype(np.float32)
+    got = nonlocal_apply(torch.from_numpy(u[None]).cuda(), c, delta, form).cpu().numpy()[0]
+    want, _ = terms(u.astype(np.float64), c, delta, form)
+    np.testing.assert_allclose(got, want.astype(np.float64), rtol=0, atol=1e-7 * float(np.abs(want).max()))
