@@ -175,8 +175,6 @@ hipError_t wgrad(lsfft_fno_s* f, const Pw& p, const float* g, const float* h, in
   w.part = f->wpart;
   w.O = p.O;
   w.I = p.I;
-  w.opad = round_up(p.O, 32);
-  w.ipad = round_up(p.I, 32);
   w.B = B;
   w.V = f->V;
   w.nblk = wgrad_blocks(B, f->V);

@@ -63,27 +63,22 @@ static hipError_t allow_lds(K kernel, size_t bytes) {
 // (c = lane % 32), so every lane moves NT consecutive voxels, one per tile,
 // in one vector access, and each half-wave reads or writes 128 NT
 // contiguous bytes of one channel.  The B operand (input channels) is
-// converted to bf16 once per block and reused for every 32-row tile of
-// output channels.  NT shrinks as the input width grows (register budget).
-constexpr int kMaxKs = 16;   // ipad <= 256
-
+// converted to bf16 once per block; the kWidth output channels (lift and hidden
+// layers) are one 32-row tile.
 template <int NT> struct VecF;
-template <> struct VecF<1> { using type = float; };
 template <> struct VecF<2> { using type = float2; };
 template <> struct VecF<4> { using type = float4; };
 
 template <int NT>
 __device__ __forceinline__ void vload(const float* p, float (&v)[NT]) {
   const typename VecF<NT>::type x = *reinterpret_cast<const typename VecF<NT>::type*>(p);
-  if constexpr (NT == 1) v[0] = x;
-  else if constexpr (NT == 2) { v[0] = x.x; v[1] = x.y; }
+  if constexpr (NT == 2) { v[0] = x.x; v[1] = x.y; }
   else { v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; }
 }
 template <int NT>
 __device__ __forceinline__ void vstore(float* p, const float (&v)[NT]) {
   typename VecF<NT>::type x;
-  if constexpr (NT == 1) x = v[0];
-  else if constexpr (NT == 2) { x.x = v[0]; x.y = v[1]; }
+  if constexpr (NT == 2) { x.x = v[0]; x.y = v[1]; }
   else { x.x = v[0]; x.y = v[1]; x.z = v[2]; x.w = v[3]; }
   *reinterpret_cast<typename VecF<NT>::type*>(p) = x;
 }
@@ -96,8 +91,7 @@ __device__ __forceinline__ void vstore(float* p, const float (&v)[NT]) {
 // lane and three waves per SIMD (with both kinds of rows two, the third spills: 142
 // us): with four voxels one wave fits, 125 and 138 us.
 template <int KS, int NT, bool ADD, bool AUX>
-__global__ __launch_bounds__(256, (KS == 2 && !(ADD && AUX)) || (KS == 1 && !ADD && !AUX) ? 3 : 1) void k_pointwise(
-    PwArgs a) {
+__global__ __launch_bounds__(256, ADD && AUX ? 1 : 3) void k_pointwise(PwArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;
@@ -124,6 +118,8 @@ __global__ __launch_bounds__(256, (KS == 2 && !(ADD && AUX)) || (KS == 1 && !ADD
         for (int k = 0; k < NT; ++k) bop[s][k][j] = (__bf16)x[k];
       }
     }
+    // (a single round of kWidth channels: written straight on, the rows' addresses are
+    // kept for all sixteen and the registers spill, 107 us for 95)
     for (int ot = 0; ot < a.opad / 32; ++ot) {
       // row of accumulator entry e; rows past the last one load the last one
       auto row = [&](int e) { return ot * 32 + 8 * (e / 4) + 4 * half + (e % 4); };
@@ -184,35 +180,23 @@ __global__ __launch_bounds__(256, (KS == 2 && !(ADD && AUX)) || (KS == 1 && !ADD
   }
 }
 
-template <int KS, int NT> hipError_t pointwise(const PwArgs& a, dim3 g, hipStream_t s) {
-  if (a.add && a.aux) hipLaunchKernelGGL((k_pointwise<KS, NT, true, true>), g, 256, 0, s, a);
-  else if (a.add) hipLaunchKernelGGL((k_pointwise<KS, NT, true, false>), g, 256, 0, s, a);
-  else if (a.aux) hipLaunchKernelGGL((k_pointwise<KS, NT, false, true>), g, 256, 0, s, a);
-  else hipLaunchKernelGGL((k_pointwise<KS, NT, false, false>), g, 256, 0, s, a);
-  return hipGetLastError();
-}
-
+// lift: 16 or 32 padded input channels, nothing added; hidden layers: 32, the modes'
+// part added, backward times GELU' of the layer before it (if there is one)
 hipError_t launch_pointwise(const PwArgs& a, hipStream_t s) {
-  if (a.ipad % 16 || a.opad % 32 || a.ipad > 16 * kMaxKs || a.V % 128) return hipErrorInvalidValue;
-  const int ks = a.ipad / 16;
-  const int nt = ks <= 1 ? 4 : (ks <= 8 ? 2 : 1);
+  const bool wide = a.ipad == 32;
+  if ((a.ipad != 16 && !wide) || a.O != kWidth || a.opad != kWidth || a.V % 128 || (a.add && !wide) || (a.aux && !a.add))
+    return hipErrorInvalidValue;
+  const int nt = wide ? 2 : 4;
   const long long nblk = (long long)a.B * (a.V / (32 * nt));
   long long blocks = (nblk + 3) / 4;
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
   const dim3 g((unsigned)blocks);
-  switch (ks) {
-    case 1: return pointwise<1, 4>(a, g, s);
-    case 2: return pointwise<2, 2>(a, g, s);
-    case 4: return pointwise<4, 2>(a, g, s);
-    case 6: return pointwise<6, 2>(a, g, s);
-    case 8: return pointwise<8, 2>(a, g, s);
-    case 10: return pointwise<10, 1>(a, g, s);
-    case 12: return pointwise<12, 1>(a, g, s);
-    case 14: return pointwise<14, 1>(a, g, s);
-    case 16: return pointwise<16, 1>(a, g, s);
-    default: return hipErrorInvalidValue;
-  }
+  if (!wide) hipLaunchKernelGGL((k_pointwise<1, 4, false, false>), g, 256, 0, s, a);
+  else if (a.aux) hipLaunchKernelGGL((k_pointwise<2, 2, true, true>), g, 256, 0, s, a);
+  else if (a.add) hipLaunchKernelGGL((k_pointwise<2, 2, true, false>), g, 256, 0, s, a);
+  else hipLaunchKernelGGL((k_pointwise<2, 2, false, false>), g, 256, 0, s, a);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -227,7 +211,6 @@ int wgrad_blocks(int B, long long V) {
   return (int)(nb < kWgBlocks ? (nb < 1 ? 1 : nb) : kWgBlocks);
 }
 
-template <int TO, int TI>
 __global__ __launch_bounds__(256) void k_wgrad(WgArgs a) {
   __shared__ float red[4][1024 + 32];
   const int lane = threadIdx.x & 63;
@@ -235,14 +218,8 @@ __global__ __launch_bounds__(256) void k_wgrad(WgArgs a) {
   const int half = lane >> 5, row = lane & 31;
   const long long V = a.V;
   const long long chunks = (long long)a.B * (V / 16);
-  f32x16 acc[TO][TI];
-  float bsum[TO];
-#pragma unroll
-  for (int p = 0; p < TO; ++p) {
-    bsum[p] = 0.0f;
-#pragma unroll
-    for (int q = 0; q < TI; ++q) acc[p][q] = f32x16{0};
-  }
+  f32x16 acc = f32x16{0};
+  float bsum = 0.0f;
   for (long long c = (long long)blockIdx.x * 4 + wave; c < chunks; c += (long long)gridDim.x * 4) {
     const int b = int(c / (V / 16));
     const long long v0 = (c % (V / 16)) * 16 + half * 8;
@@ -256,61 +233,36 @@ __global__ __launch_bounds__(256) void k_wgrad(WgArgs a) {
       x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w;
       x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
     };
-    bf16x8 bop[TI];
+    bf16x8 aop, bop;
+    float x[8];
+    load8(a.h + ((long long)b * a.I + (row < a.I ? row : 0)) * V + v0, row < a.I, x);
 #pragma unroll
-    for (int q = 0; q < TI; ++q) {
-      const int i = q * 32 + row;
-      float x[8];
-      load8(a.h + ((long long)b * a.I + (i < a.I ? i : 0)) * V + v0, i < a.I, x);
+    for (int j = 0; j < 8; ++j) bop[j] = (__bf16)x[j];
+    load8(a.g + ((long long)b * a.O + (row < a.O ? row : 0)) * V + v0, row < a.O, x);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) bop[q][j] = (__bf16)x[j];
+    for (int j = 0; j < 8; ++j) {
+      bsum += x[j];
+      aop[j] = (__bf16)x[j];
     }
-#pragma unroll
-    for (int p = 0; p < TO; ++p) {
-      const int o = p * 32 + row;
-      float x[8];
-      load8(a.g + ((long long)b * a.O + (o < a.O ? o : 0)) * V + v0, o < a.O, x);
-      bf16x8 aop;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        bsum[p] += x[j];
-        aop[j] = (__bf16)x[j];
-      }
-#pragma unroll
-      for (int q = 0; q < TI; ++q) acc[p][q] = mfma(aop, bop[q], acc[p][q]);
-    }
+    acc = mfma(aop, bop, acc);
   }
-  // fixed-order sum of the four waves, tile by tile
-  float* part = a.part + (size_t)blockIdx.x * (a.opad * a.ipad + a.opad);
+  // fixed-order sum of the four waves
+  float* part = a.part + (size_t)blockIdx.x * (32 * 32 + 32);
 #pragma unroll
-  for (int p = 0; p < TO; ++p) {
-#pragma unroll
-    for (int q = 0; q < TI; ++q) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) red[wave][e * 64 + lane] = acc[p][q][e];
-      if (q == 0) red[wave][1024 + (lane & 31)] = 0.0f;
-      __syncthreads();
-      if (q == 0) {
-        // bias partial: lanes l and l + 32 hold the two halves of row l % 32
-        if (half == 0) red[wave][1024 + row] = bsum[p];
-        __syncthreads();
-        if (half == 1) red[wave][1024 + row] += bsum[p];
-        __syncthreads();
-      }
-      for (int k = threadIdx.x; k < 1024; k += 256) {
-        const float s = red[0][k] + red[1][k] + red[2][k] + red[3][k];
-        const int e = k / 64, l = k % 64;
-        const int o = p * 32 + 8 * (e / 4) + 4 * (l / 32) + (e % 4);
-        const int i = q * 32 + (l & 31);
-        part[o * a.ipad + i] = s;
-      }
-      if (q == 0 && threadIdx.x < 32)
-        part[a.opad * a.ipad + p * 32 + threadIdx.x] =
-            red[0][1024 + threadIdx.x] + red[1][1024 + threadIdx.x] + red[2][1024 + threadIdx.x] +
-            red[3][1024 + threadIdx.x];
-      __syncthreads();
-    }
+  for (int e = 0; e < 16; ++e) red[wave][e * 64 + lane] = acc[e];
+  // bias partial: lanes l and l + 32 hold the two halves of row l % 32
+  if (half == 0) red[wave][1024 + row] = bsum;
+  __syncthreads();
+  if (half == 1) red[wave][1024 + row] += bsum;
+  __syncthreads();
+  for (int k = threadIdx.x; k < 1024; k += 256) {
+    const float s = red[0][k] + red[1][k] + red[2][k] + red[3][k];
+    const int e = k / 64, l = k % 64;
+    part[(8 * (e / 4) + 4 * (l / 32) + (e % 4)) * 32 + (l & 31)] = s;
   }
+  if (threadIdx.x < 32)
+    part[1024 + threadIdx.x] = red[0][1024 + threadIdx.x] + red[1][1024 + threadIdx.x] + red[2][1024 + threadIdx.x] +
+                               red[3][1024 + threadIdx.x];
 }
 
 // Fixed-order sum of the per-block partials: a workgroup covers 16 consecutive
@@ -355,14 +307,11 @@ static hipError_t launch_wgrad_reduce(const float* part, int nblk, int O, int I,
 }
 
 hipError_t launch_wgrad(const WgArgs& a, float* gw, float* gb, hipStream_t s) {
-  if (a.V % 16 || a.opad % 32 || a.ipad % 32) return hipErrorInvalidValue;
-  const dim3 g((unsigned)a.nblk);
-  const int to = a.opad / 32, ti = a.ipad / 32;
-  if (to != 1 || ti != 1) return hipErrorInvalidValue;   // the width's layers: lift and hidden
-  hipLaunchKernelGGL((k_wgrad<1, 1>), g, 256, 0, s, a);
-  hipError_t e = hipGetLastError();
+  if (a.V % 16 || a.O > 32 || a.I > 32) return hipErrorInvalidValue;   // the width's layers: lift and hidden
+  hipLaunchKernelGGL(k_wgrad, dim3((unsigned)a.nblk), 256, 0, s, a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_wgrad_reduce(a.part, a.nblk, a.O, a.I, a.opad, a.ipad, gw, gb, s);
+  return launch_wgrad_reduce(a.part, a.nblk, a.O, a.I, 32, 32, gw, gb, s);
 }
 
 // ---------------------------------------------------------------------------

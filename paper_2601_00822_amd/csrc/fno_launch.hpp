@@ -9,10 +9,11 @@ namespace lsfft_fno {
 
 constexpr int kWidth = 32;   // channels of the hidden layers (one MFMA tile)
 
-// Pointwise layer out[b][o][v] = sum_i w[o][i] in[b][i][v] (+ bias[o])
-// (+ add[b][o][v]); then, if aux, out *= GELU'(aux[b][o][v]); if out_act,
-// out_act = GELU(out).  out may be null when only out_act is wanted.  w is bf16 [opad][ipad], zero padded (opad multiple of
-// 32, ipad multiple of 16).
+// Pointwise layer of kWidth output channels, out[b][o][v] = sum_i w[o][i]
+// in[b][i][v] (+ bias[o]) (+ add[b][o][v]); then, if aux, out *=
+// GELU'(aux[b][o][v]); if out_act, out_act = GELU(out).  out may be null when
+// only out_act is wanted.  w is bf16 [opad][ipad], zero padded, opad kWidth and ipad
+// 16 or 32; add needs ipad 32, aux needs add.
 struct PwArgs {
   const float* in;
   const __hip_bfloat16* w;
@@ -26,15 +27,15 @@ struct PwArgs {
 };
 hipError_t launch_pointwise(const PwArgs& a, hipStream_t s);
 
-// Weight gradient of a pointwise layer: per block partial sums
-// part[blk][opad][ipad] and part_b[blk][opad] of sum_{b,v} g[b][o][v] h[b][i][v]
-// and sum g[b][o][v]; then the fixed-order reduction into the packed
+// Weight gradient of a pointwise layer of at most 32 channels each way: per block
+// partial sums part[blk][32][32] and, after them, [32] of sum_{b,v} g[b][o][v]
+// h[b][i][v] and sum g[b][o][v]; then the fixed-order reduction into the packed
 // gradient gw [O][I], gb [O].
 struct WgArgs {
   const float* g;
   const float* h;
   float* part;
-  int O, I, opad, ipad, B;
+  int O, I, B;
   long long V;
   int nblk;
 };
