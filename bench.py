@@ -166,8 +166,9 @@ def run_batch_workload(args, wl):
                               "iterations / wall time"},
         "kernel_gbs": {k: round(v["gbs"], 1) for k, v in per.items()},
         "timing_region": {"seconds": elapsed_t,
-                          "note": "one batch with graphs off and a HIP event pair stamped at every kernel's start "
-                                  "and end; kernel bandwidths and the roofline come from this region"},
+                          "note": "one batch with graphs off, one launch per pass (also where the timed plan "
+                                  "transforms whole planes in one) and a HIP event pair stamped at every kernel's "
+                                  "start and end; kernel bandwidths and the roofline come from this region"},
         "roofline": roofline_field(per, dom, None),
         "autotune": {"schedule": {f"{e['kind']}/{e['len']}": e["variant"] for e in tune if e["chosen"]},
                      "us_per_launch": {f"{e['kind']}/{e['len']}/v{e['variant']}": round(e["us"], 2) for e in tune}},
@@ -426,7 +427,7 @@ def run_fno_step_workload(args, wl):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for name in ("kernels_impl.hpp", "fft_core.hpp"):
+    for name in ("kernels_impl.hpp", "fft_core.hpp", "k_plane.hip", "k_solve2d.hip"):
         with open(os.path.join(ROOT, "paper_2601_00822_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -745,7 +746,8 @@ def main() -> int:
                         "note": "algorithmic bytes of all solver kernels per iteration x iterations / wall time "
                                 "of the timed region"},
         "timing_region": {"value": nvox * iters_t / elapsed_t, "solves": steps_t,
-                          "note": "same solves with graphs off and a HIP event pair stamped at every kernel's "
+                          "note": "same solves with graphs off, one launch per pass (also where the timed plan "
+                                  "transforms whole planes in one) and a HIP event pair stamped at every kernel's "
                                   "start and end (hipExtLaunchKernelGGL); kernel durations and the roofline come "
                                   "from this region"},
         "roofline": roofline_field(per, dom, traffic),

@@ -364,16 +364,19 @@ lsfft_status lsfft_bump_forces(int prec, int dim, const int64_t* n, int nforce, 
  *            -b_k for the displacement type)
  *  G         host [nc^2], row major, symmetric
  *  g         host [nc];  gg  host, sum_k ||Gamma_k||^2
- * Allocates a small device buffer; synchronises hip_stream.  LSFFT_E_ARG for
- * bad sizes, a form other than 0 or 1, a horizon outside its range or null
- * pointers. */
+ * Its tables and partial sums are in a device scratch inside the library (one
+ * per GPU, 6.1 MiB, held by one call at a time; a call that finds it held
+ * allocates).  Synchronises hip_stream.  LSFFT_E_ARG for bad sizes, a form
+ * other than 0 or 1, a horizon outside its range or null pointers. */
 lsfft_status lsfft_nonlocal_normal_equations(int prec, int dim, const int64_t* n, int nsample, const void* u,
                                              const void* gamma, int degree, int form, double delta, double* G,
                                              double* g, double* gg, void* hip_stream);
 
 /* out = L_c[u] for nsample fields (device [nsample][d][N] each, in prec; out
- * must not overlap u); c host [nc].  Allocates a small device buffer;
- * synchronises hip_stream. */
+ * must not overlap u); c host [nc].  Tables in the same scratch; synchronises
+ * hip_stream.  Both forms of the operator take a rigid offset of u without
+ * loss: the matrix form adds weighted differences, the scalar form subtracts
+ * u(x) per group of offsets that share weights. */
 lsfft_status lsfft_nonlocal_apply(int prec, int dim, const int64_t* n, int nsample, const void* u, int degree,
                                   int form, const double* c, double delta, void* out, void* hip_stream);
 

@@ -107,7 +107,7 @@ __device__ __forceinline__ void row_table(const Geom& G, const Spot& s, int2* ta
 // Stage one component's box (entries IL apart): tpr threads per row.  Eight
 // rows' loads are in flight before the first is stored: one at a time, with
 // the row's coordinates stepped along, the scalar normal equations took 468
-// us instead of 322.
+// us instead of 327.
 template <int IL, typename T>
 __device__ __forceinline__ void stage(const Geom& G, const T* __restrict__ u, const Spot& s, const int2* tab, T* lds) {
   constexpr int U = 8;
